@@ -203,109 +203,188 @@ __global__ __launch_bounds__(kBlock) void k_pbound(const double *__restrict__ M,
   ub[x] = acc * (1.0 + slack);
 }
 
-__device__ __forceinline__ bool kv_better(double ka, int ia, double kb, int ib) {
+// The library's choice (greedy_width 0) starts each separation round with a
+// batch of 2 and widens the round's later batches to 4, 8, 16.  Measured with
+// fixed widths on R-MAT scale 22, k = 100: 214 gain evaluations in about 105
+// rounds at width 2 (the two best bounds are nearly always the exact top
+// two), 0.97 s, against 1.10 s at 4, 1.35 s at 8 and 1.79 s at 16; on BA
+// n = 1e6, k = 10: 4.0 ms at 2 against 6.2 ms at 8.  On graphs of at most
+// 2^20 arcs a step is launch-bound whatever its width, so rounds start at 8
+// there (Erdos-Renyi n = 1000, k = 5: 2.4 ms at 8 against 4.2 ms at 2).
+constexpr int kWidthFirst = 2, kWidthSmall = 8, kWidthMax = 16;
+constexpr int64_t kSmallArcs = int64_t(1) << 20;
+
+// Selection keys: the bits of a nonnegative double order as the value does, so
+// a bound's key is its bits + 1 and 0 marks an empty slot (id INT_MAX); larger
+// key first, then smaller id.
+__device__ __forceinline__ uint64_t key_of(double v) {
+  return (uint64_t)__double_as_longlong(v + 0.0) + 1;  // + 0.0: -0 orders as 0
+}
+
+__device__ __forceinline__ bool key_better(uint64_t ka, int ia, uint64_t kb, int ib) {
   return ka > kb || (ka == kb && ia < ib);
 }
 
-// K rounds of block-wide argmax over E register-resident (key, id) pairs per
-// thread; writes the block's top K (key descending, id ascending).
+constexpr int kTopMax = kWidthMax + 1;  // most pairs one selection returns
+
+// Largest key / smallest id over a wavefront, in every lane: row shifts and
+// row broadcasts (DPP) leave the result in lane 63.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint64_t dpp_max_step(uint64_t x) {
+  const unsigned lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)x, CTRL, ROWS, 0xf, false);
+  const unsigned hi = __builtin_amdgcn_update_dpp(0, (int)(x >> 32), CTRL, ROWS, 0xf, false);
+  const uint64_t y = ((uint64_t)hi << 32) | lo;
+  return y > x ? y : x;
+}
+
+__device__ __forceinline__ uint64_t wave_max_key(uint64_t x) {
+  x = dpp_max_step<0x111, 0xf>(x);  // row_shr:1, 2, 4, 8
+  x = dpp_max_step<0x112, 0xf>(x);
+  x = dpp_max_step<0x114, 0xf>(x);
+  x = dpp_max_step<0x118, 0xf>(x);
+  x = dpp_max_step<0x142, 0xa>(x);  // row_bcast:15, 31
+  x = dpp_max_step<0x143, 0xc>(x);
+  const unsigned lo = __builtin_amdgcn_readlane((int)(unsigned)x, 63);
+  const unsigned hi = __builtin_amdgcn_readlane((int)(x >> 32), 63);
+  return ((uint64_t)hi << 32) | lo;
+}
+
+__device__ __forceinline__ int wave_min_id(int x) {
+  x = min(x, __builtin_amdgcn_update_dpp(INT_MAX, x, 0x111, 0xf, 0xf, false));
+  x = min(x, __builtin_amdgcn_update_dpp(INT_MAX, x, 0x112, 0xf, 0xf, false));
+  x = min(x, __builtin_amdgcn_update_dpp(INT_MAX, x, 0x114, 0xf, 0xf, false));
+  x = min(x, __builtin_amdgcn_update_dpp(INT_MAX, x, 0x118, 0xf, 0xf, false));
+  x = min(x, __builtin_amdgcn_update_dpp(INT_MAX, x, 0x142, 0xa, 0xf, false));
+  x = min(x, __builtin_amdgcn_update_dpp(INT_MAX, x, 0x143, 0xc, 0xf, false));
+  return __builtin_amdgcn_readlane(x, 63);
+}
+
+// Top K <= kTopMax of E register-resident (key, id) pairs per thread; writes
+// the block's top K (key descending, id ascending; -inf, INT_MAX past the
+// last).  Bound by latency, not by reads: each wavefront takes its own top K
+// by K rounds over its lanes' best pairs -- only the lane that won scans its
+// E pairs again -- without a block barrier, and the four lists are merged by
+// rank (each entry counts the better ones).  With K block-wide rounds between
+// barriers and loads guarded by the conditions they fed, a selection took
+// 17 us (n = 1000, K = 9), 24 + 14 us (n = 100,000) and 15 + 6 us (n = 10^6,
+// K = 3); now 7.9, 7.7 + 7.6 and 8.1 + 3.9 us.
 template <int E>
-__device__ void block_topk(double (&kv)[E], int (&iv)[E], int K, double *ok, int *oi) {
-  __shared__ double sk[kBlock / 64];
-  __shared__ int si[kBlock / 64];
+__device__ void block_topk(const uint64_t (&kv)[E], const int (&iv)[E], int K, double *ok,
+                           int *oi) {
+  constexpr int W = kBlock / 64;
+  __shared__ uint64_t sk[W * kTopMax];
+  __shared__ int si[W * kTopMax];
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  for (int r = 0; r < K; ++r) {
-    double bk = -INFINITY;
-    int bi = INT_MAX;
+  uint64_t bk = 0;
+  int bi = INT_MAX;
 #pragma unroll
-    for (int q = 0; q < E; ++q)
-      if (kv_better(kv[q], iv[q], bk, bi)) {
-        bk = kv[q];
-        bi = iv[q];
-      }
-    for (int off = 32; off > 0; off >>= 1) {
-      const double k2 = __shfl_xor(bk, off, 64);
-      const int i2 = __shfl_xor(bi, off, 64);
-      if (kv_better(k2, i2, bk, bi)) {
-        bk = k2;
-        bi = i2;
-      }
+  for (int q = 0; q < E; ++q)
+    if (key_better(kv[q], iv[q], bk, bi)) {
+      bk = kv[q];
+      bi = iv[q];
     }
+  for (int r = 0; r < K; ++r) {
+    const uint64_t wk = wave_max_key(bk);
+    const int wi = wave_min_id(bk == wk ? bi : INT_MAX);
     if (lane == 0) {
-      sk[wave] = bk;
-      si[wave] = bi;
+      sk[wave * K + r] = wk;
+      si[wave * K + r] = wi;
     }
-    __syncthreads();
-    double wk = sk[0];
-    int wi = si[0];
-    for (int w = 1; w < kBlock / 64; ++w)
-      if (kv_better(sk[w], si[w], wk, wi)) {
-        wk = sk[w];
-        wi = si[w];
-      }
-    __syncthreads();
-    if (wi != INT_MAX) {
+    if (wk != 0 && bk == wk && bi == wi) {  // ids are distinct: one lane
+      bk = 0;
+      bi = INT_MAX;
 #pragma unroll
       for (int q = 0; q < E; ++q)
-        if (iv[q] == wi) {
-          kv[q] = -INFINITY;
-          iv[q] = INT_MAX;
+        if (key_better(wk, wi, kv[q], iv[q]) && key_better(kv[q], iv[q], bk, bi)) {
+          bk = kv[q];
+          bi = iv[q];
         }
     }
-    if (t == 0) {
-      ok[r] = wk;
-      oi[r] = wi;
+  }
+  __syncthreads();
+  if (t < W * K) {
+    const uint64_t k = sk[t];
+    const int i = si[t];
+    int rank = 0;
+    for (int e = 0; e < W * K; ++e)
+      rank += key_better(sk[e], si[e], k, i) || (sk[e] == k && si[e] == i && e < t);
+    if (rank < K) {
+      ok[rank] = k ? __longlong_as_double((long long)(k - 1)) : -INFINITY;
+      oi[rank] = i;
     }
   }
 }
 
-constexpr int kTopE = 16;  // elements per thread in the selection kernels
+// Elements per thread in the selection kernels: 16, or 4 for up to
+// kTopSmall elements, where a launch is one latency chain and the scans of 16
+// pairs per thread are most of it (n = 100,000, K = 9: 17.8 us
+// at 16, 7.7 us at 4; n = 10^6, K = 3 at 16: 8.1 us).
+constexpr int kTopE = 16, kTopESmall = 4;
+constexpr int kTopSmall = 1 << 17;
 
 // Eligible: bound >= 0 (not in S), not evaluated in this round, and (for the
 // stochastic variant) in the current sample.
 // Keys carry the caller's vertex id, so ties break by it whatever the
 // internal vertex order is.
+template <int kE>
 __global__ __launch_bounds__(kBlock) void k_topk_ub(const double *__restrict__ ub,
                                                     const int *__restrict__ done, int round,
                                                     const int *__restrict__ sampled, int pick,
                                                     const int *__restrict__ orig, int n, int K,
                                                     double *ok, int *oi) {
-  double kv[kTopE];
-  int iv[kTopE];
-  const int base = blockIdx.x * kBlock * kTopE + threadIdx.x;
+  uint64_t kv[kE];
+  int iv[kE];
+  const int base = blockIdx.x * kBlock * kE + threadIdx.x;
+  // every load at a clamped index and before the first use: guarded by the
+  // conditions they feed, the 3 x 16 loads waited for one another
+  double u[kE];
+  int dn[kE], sm[kE];
 #pragma unroll
-  for (int q = 0; q < kTopE; ++q) {
-    const int x = base + q * kBlock;
-    kv[q] = -INFINITY;
-    iv[q] = INT_MAX;
-    if (x < n) {
-      const double u = ub[x];
-      if (u >= 0.0 && done[x] != round && (!sampled || sampled[x] == pick)) {
-        kv[q] = u;
-        iv[q] = orig[x];
-      }
-    }
+  for (int q = 0; q < kE; ++q) u[q] = ub[min(base + q * kBlock, n - 1)];
+#pragma unroll
+  for (int q = 0; q < kE; ++q) dn[q] = done[min(base + q * kBlock, n - 1)];
+#pragma unroll
+  for (int q = 0; q < kE; ++q) iv[q] = orig[min(base + q * kBlock, n - 1)];
+#pragma unroll
+  for (int q = 0; q < kE; ++q) sm[q] = pick;
+  if (sampled) {
+#pragma unroll
+    for (int q = 0; q < kE; ++q) sm[q] = sampled[min(base + q * kBlock, n - 1)];
   }
-  block_topk<kTopE>(kv, iv, K, ok + (size_t)blockIdx.x * K, oi + (size_t)blockIdx.x * K);
+#pragma unroll
+  for (int q = 0; q < kE; ++q) {
+    const bool el = base + q * kBlock < n && u[q] >= 0.0 && dn[q] != round && sm[q] == pick;
+    kv[q] = el ? key_of(u[q]) : 0;
+    iv[q] = el ? iv[q] : INT_MAX;
+  }
+  block_topk<kE>(kv, iv, K, ok + (size_t)blockIdx.x * K, oi + (size_t)blockIdx.x * K);
 }
 
+template <int kE>
 __global__ __launch_bounds__(kBlock) void k_topk_pairs(const double *__restrict__ ik,
                                                        const int *__restrict__ ii, int count,
                                                        int K, double *ok, int *oi) {
-  double kv[kTopE];
-  int iv[kTopE];
-  const int base = blockIdx.x * kBlock * kTopE + threadIdx.x;
+  uint64_t kv[kE];
+  int iv[kE];
+  const int base = blockIdx.x * kBlock * kE + threadIdx.x;
+  double u[kE];  // unconditional loads, as in k_topk_ub
 #pragma unroll
-  for (int q = 0; q < kTopE; ++q) {
-    const int x = base + q * kBlock;
-    kv[q] = -INFINITY;
-    iv[q] = INT_MAX;
-    if (x < count) {
-      kv[q] = ik[x];
-      iv[q] = ii[x];
-    }
+  for (int q = 0; q < kE; ++q) u[q] = ik[min(base + q * kBlock, count - 1)];
+#pragma unroll
+  for (int q = 0; q < kE; ++q) iv[q] = ii[min(base + q * kBlock, count - 1)];
+#pragma unroll
+  for (int q = 0; q < kE; ++q) {
+    const bool el = base + q * kBlock < count && iv[q] != INT_MAX;
+    kv[q] = el ? key_of(u[q]) : 0;
+    iv[q] = el ? iv[q] : INT_MAX;
   }
-  block_topk<kTopE>(kv, iv, K, ok + (size_t)blockIdx.x * K, oi + (size_t)blockIdx.x * K);
+  block_topk<kE>(kv, iv, K, ok + (size_t)blockIdx.x * K, oi + (size_t)blockIdx.x * K);
+}
+
+// Blocks of a selection's first launch over n bounds.
+static int topk_blocks(int n) {
+  const int e = n > kTopSmall ? kTopE : kTopESmall;
+  return (n + kBlock * e - 1) / (kBlock * e);
 }
 
 // Candidates of a batch: cand_col[x_c] = c (value=1) or -1 (value=0).
@@ -570,17 +649,6 @@ void greedy_forget(const ged_graph *g) {
   g_greedy.erase(g);
 }
 
-// The library's choice (greedy_width 0) starts each separation round with a
-// batch of 2 and widens the round's later batches to 4, 8, 16.  Measured with
-// fixed widths on R-MAT scale 22, k = 100: 214 gain evaluations in about 105
-// rounds at width 2 (the two best bounds are nearly always the exact top
-// two), 0.97 s, against 1.10 s at 4, 1.35 s at 8 and 1.79 s at 16; on BA
-// n = 1e6, k = 10: 4.0 ms at 2 against 6.2 ms at 8.  On graphs of at most
-// 2^20 arcs a step is launch-bound whatever its width, so rounds start at 8
-// there (Erdos-Renyi n = 1000, k = 5: 2.4 ms at 8 against 4.2 ms at 2).
-constexpr int kWidthFirst = 2, kWidthSmall = 8, kWidthMax = 16;
-constexpr int64_t kSmallArcs = int64_t(1) << 20;
-
 int greedy_width_for(const ged_graph *g) {
   if (g->greedy_width > 0) return g->greedy_width;
   return g->nnz <= kSmallArcs ? kWidthSmall : kWidthFirst;
@@ -621,7 +689,7 @@ size_t greedy_footprint(ged_graph *g, int ell_max, int k) {
   while (cap < ell_max) cap *= 2;
   b += 8 * n * (size_t)(cap + 1) * (directed ? 2 : 1);  // miss levels (both chains)
   b += 2 * 4 * n;                        // mc32
-  const size_t nb0 = (n + kBlock * kTopE - 1) / (kBlock * kTopE), K = Cm + 1;
+  const size_t nb0 = (size_t)topk_blocks((int)n), K = Cm + 1;
   b += 2 * nb0 * K * (8 + 4);            // top-K pairs
   b += 64 * 12 + 4;                      // cand_dev, gains, wl2_n
   if (split) {
@@ -801,22 +869,25 @@ static void chains_for(GreedyCtx &c, int ell) {
 // Top-K eligible (bound, caller id) pairs, best first, into host arrays.
 static int select_topk(GreedyCtx &c, int K, int round, const int *sampled, int pick, double *hk,
                        int *hi) {
-  const int chunk = kBlock * kTopE;
   // the launch that leaves one block writes its K pairs straight into the
   // coherent host buffer
   double *sk = c.h_small.as<double>();
   int *si = reinterpret_cast<int *>(sk + 64);
-  int nb = (c.n + chunk - 1) / chunk;
-  hipLaunchKernelGGL(k_topk_ub, dim3(nb), dim3(kBlock), 0, c.st, c.ub.as<const double>(),
-                     c.done.as<const int>(), round, sampled, pick, c.g->d_old_id.as<const int>(),
-                     c.n, K, nb == 1 ? sk : c.topk_k[0].as<double>(),
+  int nb = topk_blocks(c.n);
+  hipLaunchKernelGGL(c.n > kTopSmall ? k_topk_ub<kTopE> : k_topk_ub<kTopESmall>, dim3(nb),
+                     dim3(kBlock), 0, c.st, c.ub.as<const double>(), c.done.as<const int>(),
+                     round, sampled, pick, c.g->d_old_id.as<const int>(), c.n, K,
+                     nb == 1 ? sk : c.topk_k[0].as<double>(),
                      nb == 1 ? si : c.topk_i[0].as<int>());
   GED_HIP(hipGetLastError());
   int cur = 0, count = nb * K;
   while (nb > 1) {
-    nb = (count + chunk - 1) / chunk;
-    hipLaunchKernelGGL(k_topk_pairs, dim3(nb), dim3(kBlock), 0, c.st,
-                       c.topk_k[cur].as<const double>(), c.topk_i[cur].as<const int>(), count, K,
+    // one block of kTopE pairs per thread rather than another launch
+    const int e = count > kBlock * kTopESmall ? kTopE : kTopESmall;
+    nb = (count + kBlock * e - 1) / (kBlock * e);
+    hipLaunchKernelGGL(e == kTopE ? k_topk_pairs<kTopE> : k_topk_pairs<kTopESmall>, dim3(nb),
+                       dim3(kBlock), 0, c.st, c.topk_k[cur].as<const double>(),
+                       c.topk_i[cur].as<const int>(), count, K,
                        nb == 1 ? sk : c.topk_k[cur ^ 1].as<double>(),
                        nb == 1 ? si : c.topk_i[cur ^ 1].as<int>());
     GED_HIP(hipGetLastError());
@@ -1225,7 +1296,7 @@ int greedy_run(ged_graph *g, int32_t k, double alpha, double eps, double eta, ui
   }
   c.cand_dev.ensure(sizeof(int) * 64);
   c.gains.ensure(sizeof(double) * 64);
-  const int nb0 = (n + kBlock * kTopE - 1) / (kBlock * kTopE);
+  const int nb0 = topk_blocks(n);
   c.topk_k[0].ensure(sizeof(double) * (size_t)nb0 * K);
   c.topk_i[0].ensure(sizeof(int) * (size_t)nb0 * K);
   c.topk_k[1].ensure(sizeof(double) * (size_t)nb0 * K);

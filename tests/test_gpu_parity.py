@@ -1266,3 +1266,26 @@ def test_keep_order_parity(ged):
     compare_greedy(kept.greedy(8, alpha, EPS), oracle.greedy(g, 8, alpha, EPS), "kept order")
     kept.close()
     relab.close()
+
+
+@pytest.mark.parametrize("n", [3, 17, 64, 1023, 1025, 4096, 4097, 9_001])
+def test_greedy_selection_ties(ged, n):
+    """Candidate selection at the edges of its wavefronts (1,024 vertices) and
+    blocks (4,096) and over the merge pass: on a cycle the bounds and gains
+    tie, so picks are decided by the caller ids (smaller first).  alpha = 1/4
+    and eps = n/16 keep the walk length at most 16 (B_ell = n 2^-ell against
+    eps/k = n/64), where every term is a multiple of 4^-16 below 2^20 and so
+    every sum is exact: the ties are exact on both sides."""
+    src = np.arange(n, dtype=np.int32)
+    g = inputs.from_edges(n, src, (src + 1) % n)
+    gg = ged.GedGraph.from_graph(g)
+    say(f"[selection ties] cycle n={n}")
+    k, eps = min(n, 4), n / 16
+    o = oracle.greedy(g, k, 0.25, eps)
+    assert max(o["ell"]) <= 16
+    for width in (0, 2, 16):
+        gg.set_greedy_width(width)
+        r = gg.greedy(k, 0.25, eps)
+        assert list(r["group"]) == list(o["group"]), (n, width)
+        assert list(r["ell"]) == list(o["ell"])
+    gg.close()
