@@ -337,14 +337,19 @@ int score_batch(ged_graph *g, const int64_t *offsets, const int32_t *members, in
   // before any capture (the host table may need a synchronisation once).  A
   // captured batch keeps the choices of the call that captured it: both
   // clear everything the pushes wrote, so later groups only differ in speed.
+  // Whether level 2 is gathered is one choice for the whole batch (its mean
+  // tile), kept with the captured graph's key.
   std::vector<char> fill((size_t)(G + C - 1) / C, 0);
   if (split && pl.s >= 2 && !pl.push3) {
     const std::vector<double> &om2 = omega2_host(g, st);
+    double sum = 0.0;
     for (size_t t = 0; t < fill.size(); ++t) {
       double v = 0.0;
       for (int64_t q = hoff[t * C]; q < hoff[std::min(G, (int)(t + 1) * C)]; ++q) v += om2[hmem[q]];
       fill[t] = split_clear_by_fill(g, pl, C, v) ? 1 : 0;
+      sum += v;
     }
+    pl.dense2 = split_dense2(g, pl, C, sum / (double)fill.size());
   }
   auto enqueue = [&]() {
     if (!split) {
@@ -401,7 +406,8 @@ int score_batch(ged_graph *g, const int64_t *offsets, const int32_t *members, in
                                    (const void *)(intptr_t)g->prep.ell, (const void *)(intptr_t)G,
                                    (const void *)(intptr_t)C,
                                    (const void *)(intptr_t)g->batch_cut_div,
-                                   (const void *)(intptr_t)pl.c16_hub};
+                                   (const void *)(intptr_t)pl.c16_hub,
+                                   (const void *)(intptr_t)pl.dense2, g->omega2_f.p};
 
   if (g->prof.on) {
     // profiling times every step launch with events: run the batch eagerly

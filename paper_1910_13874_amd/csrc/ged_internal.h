@@ -463,6 +463,9 @@ struct SplitPlan {
   // first stored level (3) is pushed from the vertices holding level-2
   // counts instead of gathered
   bool push3 = false;
+  // level 2 gathered from the level-1 counts by a dense step instead of pushed
+  // from the group's neighbourhoods (split_dense2)
+  bool dense2 = false;
   int cut_div = 1;  // row-split threshold divisor of the dense steps' partitions
   // level-2 counts in the 16-bit layout with this hub cut (c16_pk_offset),
   // -1: plain 32-bit counts.  Batch tiles of C >= 4 columns only (c32, s = 2,
@@ -562,9 +565,10 @@ struct ged_graph {
   hipGraph_t score_graph = nullptr;
   std::vector<const void *> score_sig;  // pointers/values the captured graph depends on
   // split scoring: one captured pair per variant (third level gathered or
-  // pushed; group copied to the device or staged by the first kernel), so
-  // groups that alternate between them keep each
-  ged::SplitExec split_exec[8];
+  // pushed; group copied to the device or staged by the first kernel; stored
+  // levels 32-bit or not; second level gathered or pushed), so groups that
+  // alternate between them keep each
+  ged::SplitExec split_exec[16];
   hipEvent_t score_done = nullptr;  // recorded after the result copy
   // batched scoring: tile width and row-split threshold divisor (0 = autotune)
   int32_t batch_tile = 0;
@@ -583,6 +587,7 @@ struct ged_graph {
   double served_alpha = 0, served_eps = 0;
   // split scoring
   ged::DBuf omega2;             // uint64 [n] walks of length 2 ending at v (unweighted)
+  ged::DBuf omega2_f;           // the same as doubles [n] (injected by a gathered level 2)
   bool omega2_ready = false;
   // omega_i(v) for i = 3 .. omega_top, exact integers as doubles [(omega_top-2)*n];
   // omega_fit = largest i <= omega_top with max_v omega_j(v) < 2^32 for 3 <= j <= i
@@ -734,6 +739,9 @@ void split_tile_clear(ged_graph *g, SplitWs &w, const SplitPlan &pl, int C, cons
 // sum of omega_2 over the tile's members, a bound on the arcs its level-2
 // push wrote along.
 bool split_clear_by_fill(const ged_graph *g, const SplitPlan &pl, int C, double push2_arcs);
+// Is level 2 of a tile of C columns cheaper gathered from level 1 by a dense
+// step than pushed?  push2_arcs as above.
+bool split_dense2(const ged_graph *g, const SplitPlan &pl, int C, double push2_arcs);
 // All four phases in order on one stream.  profile = false launches without
 // profiling events (the server enqueues tiles from its own thread).
 void enqueue_split_tile(ged_graph *g, SplitWs &w, const SplitPlan &pl, int C,

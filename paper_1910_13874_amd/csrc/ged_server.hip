@@ -327,9 +327,11 @@ static bool lane_launch_split(ged_server *s, Lane &L) {
   // width, so a tile of one request on a large graph runs as one column
   int W = 1;
   while (W < nc) W *= 2;
-  enqueue_split_tile(g, L.sw, L.pl, W, d_offs, d_mem, d_col, 0, nc, (int64_t)m,
+  SplitPlan pl = L.pl;
+  pl.dense2 = split_dense2(g, pl, W, om2);
+  enqueue_split_tile(g, L.sw, pl, W, d_offs, d_mem, d_col, 0, nc, (int64_t)m,
                      L.tmask.as<uint64_t>(), L.acc.as<double>(), L.st, false,
-                     split_clear_by_fill(g, L.pl, W, om2));
+                     split_clear_by_fill(g, pl, W, om2));
   GED_HIP(hipMemcpyAsync(L.h_acc.p, L.acc.p, sizeof(double) * nc, hipMemcpyDeviceToHost, L.st));
   GED_HIP(hipEventRecord(L.ev, L.st));
   L.inflight = true;

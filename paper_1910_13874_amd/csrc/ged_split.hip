@@ -394,10 +394,11 @@ __device__ __forceinline__ void block_max_sum(unsigned long long &m, unsigned lo
   }
 }
 
-// *sum (zeroed by the caller) receives sum_v omega_2(v).
+// *sum (zeroed by the caller) receives sum_v omega_2(v); out_d the values as
+// doubles (exact: omega_2 <= max_deg^2 < 2^53 wherever they are read).
 __global__ __launch_bounds__(kBlock) void k_omega2(const int *__restrict__ rp,
                                                    const int *__restrict__ ci, int n,
-                                                   unsigned long long *out,
+                                                   unsigned long long *out, double *out_d,
                                                    unsigned long long *sum) {
   const int lane = threadIdx.x & 63;
   const int64_t nw = (int64_t)gridDim.x * (kBlock / 64);
@@ -409,7 +410,10 @@ __global__ __launch_bounds__(kBlock) void k_omega2(const int *__restrict__ rp,
       s += (unsigned long long)(rp[u + 1] - rp[u]);
     }
     for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-    if (lane == 0) out[v] = s;
+    if (lane == 0) {
+      out[v] = s;
+      out_d[v] = (double)s;
+    }
     acc += s;
   }
   block_max_sum(m, acc);
@@ -511,6 +515,7 @@ static void ensure_omega2(ged_graph *g, hipStream_t st) {
   if (g->omega2_ready) return;
   const int64_t n = g->n;
   g->omega2.ensure(sizeof(uint64_t) * (size_t)n);
+  g->omega2_f.ensure(sizeof(double) * (size_t)n);
   DBuf sum;
   sum.ensure(sizeof(unsigned long long));
   launch_fill_i32(sum.as<int>(), 0, 2, st);
@@ -518,7 +523,7 @@ static void ensure_omega2(ged_graph *g, hipStream_t st) {
       1, std::min<int64_t>(2048, (n + kBlock / 64 - 1) / (kBlock / 64)));
   hipLaunchKernelGGL(k_omega2, dim3(og), dim3(kBlock), 0, st, g->rp.as<const int>(),
                      g->ci.as<const int>(), (int)n, g->omega2.as<unsigned long long>(),
-                     sum.as<unsigned long long>());
+                     g->omega2_f.as<double>(), sum.as<unsigned long long>());
   GED_HIP(hipGetLastError());
   unsigned long long hs = 0;
   GED_HIP(hipMemcpyAsync(&hs, sum.p, sizeof(hs), hipMemcpyDeviceToHost, st));
@@ -885,7 +890,8 @@ static void push_phase(ged_graph *g, SplitWs &w, const SplitPlan &pl, int C, con
                        int64_t tile_members, const uint64_t *tmask, hipStream_t st) {
   const int *rp = g->rp.as<const int>(), *ci = g->ci.as<const int>();
   CT *c1 = w.cnt1.as<CT>();
-  CT *c2 = pl.s >= 2 ? w.cnt2.as<CT>() : nullptr;
+  // dense2: only level 1 is pushed here, split_dense gathers level 2
+  CT *c2 = pl.s >= 2 && !pl.dense2 ? w.cnt2.as<CT>() : nullptr;
   // pushed level 3: 32-bit counts only (push3 implies lv32, hence CT = uint32)
   CT *l3 = pl.push3 ? w.lv.as<CT>() : nullptr;
   uint64_t *wl3 = l3 ? w.wl3.as<uint64_t>() : nullptr;
@@ -982,6 +988,19 @@ void split_dense(ged_graph *g, SplitWs &w, const SplitPlan &pl, int C, const uin
   a.C = C;
   a.tmask = tmask;
   a.accum = 0;
+  if (pl.dense2) {
+    // level 2 from the level-1 counts: the integers the push would add
+    // (members: omega_2), every row written
+    a.alpha = 1.0;
+    a.inj = g->omega2_f.as<const double>();
+    a.Xc32 = static_cast<const uint32_t *>(c1);
+    a.Y32 = cw.cnt2.as<uint32_t>();
+    if (profile)
+      run_step(g, pn, a, IN_CNT32, OUT_TILE32, st);
+    else
+      launch_step(pn, a, IN_CNT32, OUT_TILE32, st);
+    a.Y32 = nullptr;
+  }
   // 16-bit level-2 counts: the level-3 gather reads them (IN_CNT16), the
   // combining step reads their rows (OUT_COMBINE16), and the last stored
   // level gets a 16-bit copy (OUT_TILE32H) that the combining step gathers
@@ -1135,11 +1154,29 @@ bool split_clear_by_fill(const ged_graph *g, const SplitPlan &pl, int C, double 
   return push2_arcs * 64.0 > (double)g->n * C * (cb + cb2);
 }
 
+// A push adds one scattered 4-byte atomic per arc: measured 20 G adds/s on
+// R-MAT scale 20 and BA n = 2e6 tiles (50 ps each).  A dense step reads 4C
+// bytes per arc at 7 TB/s of lines (0.57 C ps per arc at C >= 8) and no arc
+// in less than 4 ps (one row request).  Level 2 is gathered where its push
+// would cost more than twice that -- the factor keeps the push where it
+// overlaps the dense levels of the tile before (batches) or the estimate,
+// which counts arcs into members and repeats, is near the line.  R-MAT scale
+// 20, 32 columns of |S| ~ U[1, 100]: 64 M adds, 3.0 ms pushed (and the dense
+// step beside it slowed from 0.5 to 3.4 ms); the batch of 250 groups took
+// 36.5 ms pushed, 16.5 ms gathered.
+bool split_dense2(const ged_graph *g, const SplitPlan &pl, int C, double push2_arcs) {
+  if (pl.s != 2 || !pl.c32 || pl.push3 || pl.c16_hub >= 0 || g->weighted) return false;
+  // one column of at most 2^20 arcs: either way one launch of a few us
+  if (C == 1 && g->nnz <= (int64_t(1) << 20)) return false;
+  return push2_arcs * 50.0 > 2.0 * (double)g->nnz * std::max(4.0, 0.57 * C);
+}
+
 void split_tile_clear(ged_graph *g, SplitWs &w, const SplitPlan &pl, int C, const int64_t *offs,
                       const int *mem, const int *mcol, int g0, int nc, int64_t tile_members,
                       uint64_t *tmask, hipStream_t st, bool fill) {
   const int mgrid = grid_for(tile_members, kPushGrid);
-  if (fill && pl.s >= 2 && !pl.push3) {
+  // a gathered level 2 has no worklist to replay
+  if ((fill || pl.dense2) && pl.s >= 2 && !pl.push3) {
     // the two count levels of this width, the members' column bits and the
     // worklist length: everything the pushes wrote
     const size_t words = (size_t)g->n * C * (pl.c32 ? 1 : 2);
@@ -1261,6 +1298,12 @@ int split_score(ged_graph *g, const int32_t *S, int32_t s_len, double *out) {
     for (int v : mem) b += g->push_bound[(size_t)v];
     pl.push3 = b <= (double)push3_max_arcs(g);
   }
+  if (pl.s == 2 && !pl.push3) {
+    const std::vector<double> &om2 = omega2_host(g, st);
+    double v = 0.0;
+    for (int x : mem) v += om2[(size_t)x];
+    pl.dense2 = split_dense2(g, pl, 1, v);
+  }
   split_fit(g, g->split_ws, pl, 1, split_wl_need(g, deg_sum), st);
   // a fixed worklist grid, so the captured graph serves every group
   g->split_ws.wl_blocks = 256;
@@ -1321,8 +1364,10 @@ int split_score(ged_graph *g, const int32_t *S, int32_t s_len, double *out) {
           g->prep.t_levels.p, g->prep.tr.p, g->omega2.p,
           g->omega_lv.p, g->out_host.p, (const void *)st, abits, (const void *)(intptr_t)g->prep.ell,
           (const void *)(intptr_t)cap, (const void *)(uintptr_t)w.wl_cap,
-          (const void *)(intptr_t)1 /* split */, (const void *)(intptr_t)pl.lv32};
-      SplitExec &x = g->split_exec[(pl.push3 ? 1 : 0) + (staged ? 2 : 0) + (pl.lv32 ? 4 : 0)];
+          (const void *)(intptr_t)1 /* split */, (const void *)(intptr_t)pl.lv32,
+          (const void *)(intptr_t)pl.dense2, g->omega2_f.p};
+      SplitExec &x = g->split_exec[(pl.push3 ? 1 : 0) + (staged ? 2 : 0) + (pl.lv32 ? 4 : 0) +
+                                   (pl.dense2 ? 8 : 0)];
       if (x.exec && sig != x.sig) x.drop();
       if (!x.exec) {
         capture(st, enqueue_main, &x.graph, &x.exec);

@@ -1289,3 +1289,73 @@ def test_greedy_selection_ties(ged, n):
         assert list(r["group"]) == list(o["group"]), (n, width)
         assert list(r["ell"]) == list(o["ell"])
     gg.close()
+
+
+@pytest.mark.parametrize("name,tile", [("er3k", 1), ("er3k", 2), ("er3k", 64), ("multi", 8),
+                                       ("rmat16", 32)])
+def test_batch_gathered_level2(ged, name, tile):
+    """A batch whose members' level-2 push would be long gathers level 2 from
+    the level-1 counts instead: the same integers, so a group's score does not
+    change by a bit with the batch it is in (same tile width), and equals the
+    oracle's; one more step per tile shows which way level 2 went."""
+    if name == "multi":  # every edge twice, a third of them three times
+        e = inputs.erdos_renyi(2000, 8000, 3)
+        rows = np.repeat(np.arange(e.n), np.diff(e.row_ptr))
+        lo, hi = np.minimum(rows, e.col_idx), np.maximum(rows, e.col_idx)
+        rep = np.where((lo + hi) % 3 == 0, 3, 2)
+        g = inputs.Graph(n=e.n, row_ptr=np.concatenate([[0], np.cumsum(
+            np.bincount(rows, weights=rep, minlength=e.n))]).astype(np.int64),
+            col_idx=np.repeat(e.col_idx, rep).astype(np.int32))
+    else:
+        g = inputs.erdos_renyi(3000, 15000, 5) if name == "er3k" else inputs.workload_graph(name)
+    gg = ged.GedGraph.from_graph(g)
+    gg.set_count16(-1)  # the 16-bit layout keeps the push
+    gg.set_batch_tile(tile)
+    gg.set_batch_row_cut(1)
+    alpha = g.default_alpha()
+    eps = 1e-2 if name == "rmat16" else EPS
+    # the rare low-degree vertices: a tile of them stays below the line
+    low = np.argsort(g.degrees, kind="stable")
+    low = low[g.degrees[low] > 0][:4].astype(np.int32)
+    few = [low[:1], low[1:2], np.zeros(0, np.int32)]
+    big = [np.sort(np.random.default_rng(1).permutation(g.n)[:700]).astype(np.int32),
+           np.arange(g.n, dtype=np.int32)]
+
+    def batch(groups):
+        off = np.concatenate([[0], np.cumsum([len(S) for S in groups])]).astype(np.int64)
+        mem = np.concatenate(groups).astype(np.int32)
+        gg.profile_enable(True)
+        s = gg.score_batch(off, mem, alpha, eps)
+        n_steps = gg.profile_read()["launches"]
+        gg.profile_enable(False)
+        assert np.array_equal(s, gg.score_batch(off, mem, alpha, eps))  # captured replay
+        return s, n_steps / -(-len(groups) // tile)
+
+    gg.score_batch(np.array([0, 1]), low[:1], alpha, eps)
+    s_few, n_few = batch(few)
+    s_all, n_all = batch(few + big)
+    say(f"[gathered level 2] {name} tile={tile} steps per tile {n_few} / {n_all}")
+    single = tile == 1 and g.nnz <= 1 << 20  # one column of a small graph keeps the push
+    assert n_all == n_few + (0 if single else 1)
+    assert np.array_equal(s_few, s_all[:3]) and s_all[2] == 0.0
+    for S, s in zip(few + big, s_all):
+        assert rel(s, oracle.score(g, S, alpha, eps)[0]) <= REL
+    gg.close()
+
+
+def test_score_gathered_level2(ged):
+    """Single scores on both sides of the line between a pushed and a gathered
+    level 2 on a graph above 2^20 arcs, alternating (each keeps its captured
+    graph), against the oracle."""
+    g = inputs.workload_graph("rmat16")
+    assert g.nnz > 1 << 20
+    gg = ged.GedGraph.from_graph(g)
+    alpha = g.default_alpha()
+    groups = [inputs.group(g.n, 1, 4), inputs.group(g.n, 900, 5), inputs.group(g.n, 3, 6),
+              inputs.group(g.n, 1500, 7)]  # the last is copied, not staged
+    want = [oracle.score(g, S, alpha, 1e-2)[0] for S in groups]
+    for _ in range(2):
+        for S, w in zip(groups, want):
+            say(f"[gathered level 2] rmat16 |S|={len(S)}")
+            assert rel(gg.score(S, alpha, 1e-2), w) <= REL
+    gg.close()
