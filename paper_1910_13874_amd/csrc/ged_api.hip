@@ -106,6 +106,20 @@ Partition &partition_quad(ged_graph *g, int C, int cut_div) {
   return ref;
 }
 
+Partition &partition_lower(ged_graph *g, int C, int units, int cut_div) {
+  check_cut(cut_div);
+  std::lock_guard<std::mutex> lk(g->parts_mu);
+  auto &m = g->parts_l;
+  const int key = part_key(C * 128 + units, cut_div);
+  auto it = m.find(key);
+  if (it != m.end()) return *it->second;
+  auto p = std::make_unique<Partition>();
+  build_partition(*p, g->h_rp_l, C, units, cut_div);
+  Partition &ref = *p;
+  m[key] = std::move(p);
+  return ref;
+}
+
 const Partition *partition_if_built(ged_graph *g, int C) {
   std::lock_guard<std::mutex> lk(g->parts_mu);
   auto it = g->parts.find(part_key(C, 1));
@@ -122,8 +136,8 @@ StepArgs base_args(ged_graph *g, bool reverse) {
   return a;
 }
 
-double algo_bytes(const ged_graph *g, int C, int in, int out, double extra_rows) {
-  const double n = (double)g->n, nnz = (double)g->nnz;
+double algo_bytes(const ged_graph *g, int C, int in, int out, double extra_rows, int64_t arcs) {
+  const double n = (double)g->n, nnz = (double)(arcs < 0 ? g->nnz : arcs);
   double b = 4.0 * (n + 1) + 4.0 * nnz;  // row_ptr, col_idx
   if (out == OUT_TILE32 || out == OUT_GAIN32 || out == OUT_GAINCOMB32S)
     b += 4.0 * n * C;  // Y32
@@ -233,10 +247,10 @@ void run_step(ged_graph *g, const Partition &p, const StepArgs &a, int in, int o
   hipEvent_t e0 = prof_event(g), e1 = prof_event(g);
   GED_HIP(hipEventRecord(e0, st));
   launch_step(p, a, in, out, st, e1);
-  double bytes = algo_bytes(g, a.C, in, out, extra_rows);
+  double bytes = algo_bytes(g, a.C, in, out, extra_rows, p.arcs);
   if (out == OUT_TILE32H && a.y32_marked)
     bytes -= 4.0 * (double)g->n * a.C;  // Y32 only for the counts the copy marks
-  g->prof.recs.push_back({e0, e1, a.C, bytes, (double)g->nnz * a.C, in * kKindBase + out});
+  g->prof.recs.push_back({e0, e1, a.C, bytes, (double)p.arcs * a.C, in * kKindBase + out});
 }
 
 // -------------------------------------------------------- precomputation --

@@ -407,7 +407,7 @@ int score_batch(ged_graph *g, const int64_t *offsets, const int32_t *members, in
                                    (const void *)(intptr_t)C,
                                    (const void *)(intptr_t)g->batch_cut_div,
                                    (const void *)(intptr_t)pl.c16_hub,
-                                   (const void *)(intptr_t)pl.dense2, g->omega2_f.p};
+                                   (const void *)(intptr_t)pl.dense2, g->omega2_f.p, g->ci_l.p};
 
   if (g->prof.on) {
     // profiling times every step launch with events: run the batch eagerly

@@ -192,6 +192,7 @@ constexpr int kBucketMaxUnits = 4;             // widest, bucketed by default
 struct Partition {
   int C = 0;
   int units = 0;
+  int64_t arcs = 0;  // arcs of the CSR it partitions
   int cut = 0;       // row-split threshold in arcs
   int n_blocks = 0;  // row blocks
   int n_segs = 0;    // long-row segments, or pieces (the slots of seg_out)
@@ -325,6 +326,12 @@ struct StepArgs {
   double q_alpha = 0;               // weight ratio of consecutive stored levels (OUT_COMBINE32L)
   int q_nlv = 0;
   int q_even = 0;
+  // OUT_COMBINE* of an odd walk length 2b + 1 (split_plan's quad): the step
+  // runs on the rows' lower arcs (sources before the row), tr holds
+  // sum_{c<=b} t_c + 2 t_{b+1}, inj holds t_b, and with h_b(v) the topmost
+  // level of q and y = alpha * sum the column sum takes
+  //   q + h_b*tr + [v not in S](inj[v] - h_b) * q - 2 h_b * y
+  int q_quad = 0;
   // Gain batches with speculative miss columns (OUT_GAIN, OUT_GAIN32D,
   // OUT_GAINCOMB): column c >= spec_from carries the miss chain of S plus the
   // candidate of column c - spec_from -- 0 on S and at that candidate, the
@@ -454,6 +461,9 @@ struct PrepCache {
 struct SplitPlan {
   int a = 0, r = 0, s = 0, nlv = 0;  // nlv = dense levels stored (s+1 .. a-1)
   bool even = false;                 // r == a
+  // odd length 2r + 1 of an unweighted graph: the last step is a quadratic
+  // form over each edge once (lower arcs), see combine_quad
+  bool quad = false;
   bool c32 = false;                  // counts fit 32 bits (max degree < 2^16)
   // stored levels are unscaled 32-bit counts: count_i(v) <= omega_i(v), the
   // number of all walks of length i ending at v, and max omega_i < 2^32 for
@@ -547,6 +557,15 @@ struct ged_graph {
   // are never removed, so a returned reference stays valid)
   std::mutex parts_mu;
   std::map<int, std::unique_ptr<ged::Partition>> parts, parts_r;
+  // lower arcs (undirected unweighted graphs): of each row the sources before
+  // it in the internal order, a prefix of the row; built on first use
+  std::mutex lower_mu;
+  bool lower_ready = false;
+  int64_t nnz_l = 0;
+  std::vector<int> h_rp_l;
+  ged::DBuf rp_l, ci_l;
+  int hc_rows_l = 0;            // as hc_rows, for the lower arcs
+  std::map<int, std::unique_ptr<ged::Partition>> parts_l;
   ged::PrepCache prep;
   // precomputation workspace (C = 1 steps)
   ged::StepWs pws;
@@ -632,6 +651,12 @@ Partition &partition_narrow(ged_graph *g, int C, int cut_div = 1);
 // The partition of a 16-bit (IN_CNT16) step with C >= 4 columns: blocks of
 // kLdsDoubles / (C/4) arcs; source buckets only at C <= 8.
 Partition &partition_quad(ged_graph *g, int C, int cut_div = 1);
+// The lower arcs of an undirected graph (rp_l, ci_l), built on st the first
+// time (synchronizes st then).
+void ensure_lower(ged_graph *g, hipStream_t st);
+// The partition of a step over the lower arcs gathering `units` 8-byte units
+// per arc (ensure_lower first).
+Partition &partition_lower(ged_graph *g, int C, int units, int cut_div = 1);
 // The forward C-column partition at cut_div 1 if it was built, else null
 // (builds nothing).
 const Partition *partition_if_built(ged_graph *g, int C);
@@ -661,7 +686,9 @@ void run_step(ged_graph *g, const Partition &p, const StepArgs &a, int in_mode, 
 // gathered input, the written output, the epilogue's mask reads and
 // `extra_rows` further C-wide rows of 8-byte values per vertex that the
 // epilogue streams.
-double algo_bytes(const ged_graph *g, int C, int in_mode, int out_mode, double extra_rows = 0);
+// arcs: those of the step (-1: all of the graph's).
+double algo_bytes(const ged_graph *g, int C, int in_mode, int out_mode, double extra_rows = 0,
+                  int64_t arcs = -1);
 int score_group(ged_graph *g, const int32_t *S, int32_t s_len, double alpha, double eps,
                 double *out, ged_score_info *info);
 // Drop the batched-scoring workspace of a graph that is being destroyed.

@@ -196,14 +196,16 @@ struct CombineIn {
       return *p;
   }
   // sum_{i<a} h_i(v) for column c (levels beyond the first stored one are
-  // loaded here; there are none unless ell > 8)
-  __device__ __forceinline__ double q(const StepArgs &a, int v, int c) const {
+  // loaded here; there are none unless ell > 8); top receives h_{a-1}(v)
+  __device__ __forceinline__ double q(const StepArgs &a, int v, int c, double &top) const {
     const LT *lv = static_cast<const LT *>(a.q_lv);
     const size_t o = (size_t)v * C + c, ls = (size_t)a.n * C;
     LT l0 = lv0;
     if constexpr (C16)
       if (a.q_nlv == 1) l0 = h0 != kC16Hub ? (LT)h0 : lv[o];
-    double s = (a.q_s1 * (double)c1 + a.q_s2 * (double)c2) + a.q_slv * (double)l0;
+    const double h1 = a.q_s1 * (double)c1, h2 = a.q_s2 * (double)c2, h3 = a.q_slv * (double)l0;
+    double s = (h1 + h2) + h3;
+    top = a.q_nlv > 0 ? h3 : a.q_s2 != 0.0 ? h2 : h1;
     double w = a.q_slv;
     int l = 1;
     for (; l + 3 < a.q_nlv; l += 4) {  // four loads in flight, added in level order
@@ -217,21 +219,24 @@ struct CombineIn {
         w *= a.q_alpha;
         s += w * (double)x2;
         w *= a.q_alpha;
-        s += w * (double)x3;
+        top = w * (double)x3;
+        s += top;
       } else {
         s += x0;
         s += x1;
         s += x2;
         s += x3;
+        top = x3;
       }
     }
     for (; l < a.q_nlv; ++l) {
       if constexpr (LV32) {
         w *= a.q_alpha;
-        s += w * (double)lv[l * ls + o];
+        top = w * (double)lv[l * ls + o];
       } else {
-        s += lv[l * ls + o];
+        top = lv[l * ls + o];
       }
+      s += top;
     }
     return s;
   }
@@ -278,6 +283,24 @@ __device__ __forceinline__ double combine_fin(const StepArgs &a, double q, doubl
   const double rs = a.q_even ? q + y : q;
   const double miss = inS ? 0.0 : (ta - y) * rs;
   return ((q + y) + y * trv) + miss;
+}
+
+// Odd walk length 2b + 1, undirected unweighted graphs.  The walks of length
+// 2b + 1 that avoid S are the middle arcs (u, v) with a walk of length b
+// avoiding S on either side, m_b' A m_b with m_b = t_b - h_b (0 on S), so
+//   phi_{2b+1} = 2 h_b . t_{b+1} - h_b' (alpha A) h_b,
+// and the subtracted form -- at most half of the first term, so nothing
+// cancels -- counts each edge twice: the step gathers h_b only from the
+// sources before the row (y = alpha * that sum) and the row takes -2 h_b y.
+// With levels up to 2b by the split at b (as above, a = b), the row's share is
+//   q + h_b tr + [v not in S](t_b - h_b) q - 2 h_b y,
+// q = sum_{i<=b} h_i, tr = sum_{c<=b} t_c + 2 t_{b+1}.  Half the arcs, and
+// under the degree order all of them gather from the endpoint of higher
+// degree, the rows that stay cached.
+__device__ __forceinline__ double combine_quad(double q, double top, double y, double trv,
+                                               double tb, bool inS) {
+  const double miss = inS ? 0.0 : (tb - top) * q;
+  return ((q + top * trv) + miss) - 2.0 * (top * y);
 }
 
 template <int C, int OUT>
@@ -577,8 +600,10 @@ void k_step(StepArgs a, const int4 *__restrict__ blocks,
         bool inS = false;
         if constexpr (M1) inS = (mw[(r >> 5) - (r0 >> 5)] >> (r & 31)) & 1u;
         if constexpr (CB) {
-          CombineFor<C, OUT> in = pf;
-          if (rl != rl0) in.load(a, r, c);
+          const CombineFor<C, OUT> in = pf;
+          // the next row's inputs are requested before this row's are used: a
+          // block of short rows takes several passes, each a round trip
+          if (rl + rstep < nrows) pf.load(a, r + rstep, c);
           double y;
           bool member = false;
           if constexpr (OutTraits<OUT>::gaincomb) {
@@ -596,9 +621,14 @@ void k_step(StepArgs a, const int4 *__restrict__ blocks,
                                           a.Y32 + (size_t)r * C + c);
           } else {
             member = (tmw[rl] >> c) & 1ull;
-            y = member ? in.ta : a.alpha * acc;
+            y = member && !a.q_quad ? in.ta : a.alpha * acc;
           }
-          colsum += combine_fin(a, in.q(a, r, c), y, in.trv, in.ta, member);
+          double top;
+          const double q = in.q(a, r, c, top);
+          if (!OutTraits<OUT>::gaincomb && a.q_quad)
+            colsum += combine_quad(q, top, y, in.trv, in.ta, member);
+          else
+            colsum += combine_fin(a, q, y, in.trv, in.ta, member);
         } else {
           const double y = epilogue_v<C, OUT>(a, r, c, acc, inS, TM ? tmw[rl] : 0ull,
                                               CA ? cw[rl] : -1);
@@ -781,7 +811,12 @@ __device__ __forceinline__ void fixup_tail(const StepArgs &a, int l, int r, int 
     CombineFor<C, OUT> in;
     in.load(a, r, c);
     const bool member = OutTraits<OUT>::gaincomb ? false : ((a.tmask[r] >> c) & 1ull);
-    y = combine_fin(a, in.q(a, r, c), y, in.trv, in.ta, member);
+    double top;
+    const double q = in.q(a, r, c, top);
+    if (!OutTraits<OUT>::gaincomb && a.q_quad)
+      y = combine_quad(q, top, a.alpha * acc, in.trv, in.ta, member);
+    else
+      y = combine_fin(a, q, y, in.trv, in.ta, member);
   } else if constexpr (OUT == OUT_ZERO32 || OUT == OUT_GAIN32D) {
     a.Y32[(size_t)r * C + c] = (uint32_t)y;
     a.Y[(size_t)r * C + c] = a.alpha * y;
@@ -1179,6 +1214,7 @@ void build_partition(Partition &p, const std::vector<int> &rp, int C, int units,
   plan_partition(pl, rp.data(), ci, (int)rp.size() - 1, units, cut_div, ci ? bucket_rows : 0);
   p.C = C;
   p.units = units;
+  p.arcs = rp.back();
   p.cut = pl.cut;
   p.n_blocks = pl.n_blocks;
   p.n_segs = pl.n_segs;

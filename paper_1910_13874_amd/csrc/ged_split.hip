@@ -64,6 +64,12 @@ SplitPlan split_plan(const ged_graph *g, int ell) {
   p.even = p.r == p.a;
   p.s = g->weighted ? 0 : std::min(2, p.a - 1);
   p.nlv = p.a - 1 - p.s;
+  // The quadratic form halves the arcs of the last step; the levels its rows
+  // stream stay.  It pays where the arcs outweigh them: BA n = 1e6, m = 5,
+  // ell = 7 (one stored level) 61 -> 33 us per single-group step, but on ER
+  // n = 10^4 (8 arcs per row, nine stored levels, 64 columns) the blocks only
+  // get more rows, each a chain of loads: 24 -> 50 us.
+  p.quad = !g->weighted && p.r >= 1 && p.r < p.a && g->nnz >= 4 * g->n * std::max(1, p.nlv);
   // count_2(x) <= omega_2(x) = sum_{y in N(x)} deg(y), which is at most
   // (max degree)^2, and at most nnz < 2^31 when no arc is listed twice
   p.c32 = g->max_deg < 65536 || g->simple;
@@ -456,12 +462,13 @@ __global__ __launch_bounds__(kBlock) void k_omega_next(const int *__restrict__ r
   }
 }
 
-// tr(v) = sum_{c=1..r} t_c(v), added in level order.
-__global__ void k_sum_t(const double *__restrict__ T, int64_t n, int r, double *out) {
+// tr(v) = sum_{c=1..r} t_c(v), added in level order, and with quad 2 t_{r+1}(v).
+__global__ void k_sum_t(const double *__restrict__ T, int64_t n, int r, int quad, double *out) {
   for (int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; v < n;
        v += (int64_t)gridDim.x * blockDim.x) {
     double s = 0.0;
     for (int c = 1; c <= r; ++c) s += T[(size_t)c * n + v];
+    if (quad) s += 2.0 * T[(size_t)(r + 1) * n + v];
     out[v] = s;
   }
 }
@@ -670,10 +677,11 @@ void split_tables(ged_graph *g, SplitPlan &pl, hipStream_t st) {
   if (pc.tr_r != pl.r) {
     pc.tr.ensure(sizeof(double) * (size_t)n);
     hipLaunchKernelGGL(k_sum_t, dim3(eg), dim3(kBlock), 0, st, pc.t_levels.as<const double>(),
-                       n, pl.r, pc.tr.as<double>());
+                       n, pl.r, pl.quad ? 1 : 0, pc.tr.as<double>());
     GED_HIP(hipGetLastError());
     pc.tr_r = pl.r;
   }
+  if (pl.quad) ensure_lower(g, st);
 }
 
 // Gather of the last (combining) dense level of a tile.
@@ -690,6 +698,76 @@ static Partition &step_partition(ged_graph *g, const SplitPlan &pl, int C, int i
   if (in == IN_CNT16) return partition_quad(g, C, pl.cut_div);
   return narrow_gather(C, in, g->weighted) ? partition_narrow(g, C, pl.cut_div)
                                            : partition(g, C, false, pl.cut_div);
+}
+
+// Partition of the combining step.
+static Partition &final_partition(ged_graph *g, const SplitPlan &pl, int C) {
+  const int in = final_in(pl);
+  return pl.quad ? partition_lower(g, C, gather_units(C, in, g->weighted), pl.cut_div)
+                 : step_partition(g, pl, C, in);
+}
+
+// Lower arcs: lower[v] = sources of row v before v (rows are sorted).
+__global__ void k_lower_count(const int *__restrict__ rp, const int *__restrict__ ci, int n,
+                              int *__restrict__ lower) {
+  for (int v = blockIdx.x * blockDim.x + threadIdx.x; v < n; v += gridDim.x * blockDim.x) {
+    int lo = rp[v], hi = rp[v + 1];
+    const int b = lo;
+    while (lo < hi) {
+      const int mid = lo + (hi - lo) / 2;
+      if (ci[mid] < v)
+        lo = mid + 1;
+      else
+        hi = mid;
+    }
+    lower[v] = lo - b;
+  }
+}
+
+// Eight lanes per row copy its lower arcs.
+__global__ __launch_bounds__(kBlock) void k_lower_copy(const int *__restrict__ rp,
+                                                       const int *__restrict__ ci,
+                                                       const int *__restrict__ rp_l, int n,
+                                                       int *__restrict__ ci_l) {
+  const int s = threadIdx.x & 7;
+  for (int64_t v = (blockIdx.x * (int64_t)kBlock + threadIdx.x) >> 3; v < n;
+       v += (int64_t)gridDim.x * (kBlock / 8)) {
+    const int b = rp[v], o = rp_l[v], len = rp_l[v + 1] - o;
+    for (int k = s; k < len; k += 8) ci_l[o + k] = ci[b + k];
+  }
+}
+
+void ensure_lower(ged_graph *g, hipStream_t st) {
+  std::lock_guard<std::mutex> lk(g->lower_mu);
+  if (g->lower_ready) return;
+  const int n = (int)g->n;
+  const int *rp = g->rp.as<const int>(), *ci = g->ci.as<const int>();
+  DBuf cnt;
+  cnt.ensure(sizeof(int) * (size_t)n);
+  hipLaunchKernelGGL(k_lower_count, dim3(grid_for(((int64_t)n + kBlock - 1) / kBlock, 8192)),
+                     dim3(kBlock), 0, st, rp, ci, n, cnt.as<int>());
+  GED_HIP(hipGetLastError());
+  std::vector<int> h((size_t)n + 1);
+  GED_HIP(hipMemcpyAsync(h.data() + 1, cnt.p, sizeof(int) * (size_t)n, hipMemcpyDeviceToHost, st));
+  GED_HIP(hipStreamSynchronize(st));
+  h[0] = 0;
+  for (int v = 0; v < n; ++v) h[(size_t)v + 1] += h[(size_t)v];
+  const int64_t nl = h[(size_t)n];
+  g->rp_l.ensure(sizeof(int) * (size_t)(n + 1));
+  g->ci_l.ensure(sizeof(int) * (size_t)std::max<int64_t>(1, nl));
+  GED_HIP(hipMemcpyAsync(g->rp_l.p, h.data(), sizeof(int) * (size_t)(n + 1),
+                         hipMemcpyHostToDevice, st));
+  hipLaunchKernelGGL(k_lower_copy, dim3(grid_for(((int64_t)n + kBlock / 8 - 1) / (kBlock / 8), 65536)),
+                     dim3(kBlock), 0, st, rp, ci, g->rp_l.as<const int>(), n, g->ci_l.as<int>());
+  GED_HIP(hipGetLastError());
+  GED_HIP(hipStreamSynchronize(st));
+  // the first rows' share as sources: their arcs that are lower arcs of others
+  const int hc = std::min(kHubRows, n);
+  const int64_t hub = (int64_t)g->h_rp[(size_t)hc] - h[(size_t)hc];
+  g->hc_rows_l = nl > 0 && hub * kHubShareDiv >= nl ? hc : 0;
+  g->nnz_l = nl;
+  g->h_rp_l.swap(h);
+  g->lower_ready = true;
 }
 
 // The level-3 push adds each level-2 source's count to all its neighbours:
@@ -824,6 +902,7 @@ void split_fit(ged_graph *g, SplitWs &w, const SplitPlan &pl, int C, size_t wl_n
     w.ws.fit(partition(g, C, false, pl.cut_div));
     if (pl.s >= 1 && pl.c32) w.ws.fit(step_partition(g, pl, C, IN_CNT32));
     if (pl.c16_hub >= 0) w.ws.fit(step_partition(g, pl, C, IN_CNT16));
+    w.ws.fit(final_partition(g, pl, C));
   }
   if (pl.s >= 1) {
     const size_t cb = (pl.c32 ? sizeof(uint32_t) : sizeof(uint64_t)) * nC;
@@ -881,7 +960,7 @@ void split_fit_width(ged_graph *g, SplitWs &w, const SplitPlan &pl, int C) {
   w.ws.fit(partition(g, C, false, pl.cut_div));
   if (pl.s >= 1 && pl.c32) w.ws.fit(step_partition(g, pl, C, IN_CNT32));
   if (pl.c16_hub >= 0) w.ws.fit(step_partition(g, pl, C, IN_CNT16));
-  w.ws.fit(step_partition(g, pl, C, final_in(pl)));
+  w.ws.fit(final_partition(g, pl, C));
 }
 
 template <class CT>
@@ -988,6 +1067,15 @@ void split_dense(ged_graph *g, SplitWs &w, const SplitPlan &pl, int C, const uin
   a.C = C;
   a.tmask = tmask;
   a.accum = 0;
+  // the combining step's injected level, and its arcs in the odd case
+  auto lower_args = [&](int i) {
+    a.inj = T + (size_t)(pl.quad ? i - 1 : i) * n;
+    a.q_quad = pl.quad ? 1 : 0;
+    if (!pl.quad) return;
+    a.rp = g->rp_l.as<const int>();
+    a.ci = g->ci_l.as<const int>();
+    a.hc_rows = g->hc_rows_l;
+  };
   if (pl.dense2) {
     // level 2 from the level-1 counts: the integers the push would add
     // (members: omega_2), every row written
@@ -1046,7 +1134,7 @@ void split_dense(ged_graph *g, SplitWs &w, const SplitPlan &pl, int C, const uin
           launch_step(pi, a, in, out, st);
       } else {
         a.alpha = alpha_a;
-        a.inj = T + (size_t)i * n;
+        lower_args(i);
         a.Y = nullptr;
         a.Y32 = nullptr;
         a.tr = pc.tr.as<const double>();
@@ -1065,11 +1153,12 @@ void split_dense(ged_graph *g, SplitWs &w, const SplitPlan &pl, int C, const uin
         a.Y16 = nullptr;
         a.y32_marked = 0;
         const int out = c16 ? OUT_COMBINE16 : OUT_COMBINE32L;
+        Partition &pf = final_partition(g, pl, C);
         if (profile)
-          run_step(g, pi, a, in, out, st,
+          run_step(g, pf, a, in, out, st,
                    c16 ? 0.75 + (pl.nlv == 1 ? 0.25 : 0.5 * pl.nlv) : 0.5 * (pl.s + pl.nlv));
         else
-          launch_step(pi, a, in, out, st);
+          launch_step(pf, a, in, out, st);
       }
     }
     return;
@@ -1108,6 +1197,8 @@ void split_dense(ged_graph *g, SplitWs &w, const SplitPlan &pl, int C, const uin
     } else {
       // absent inputs: index mask 0 into a valid buffer, weight 0
       const double *any = pc.tr.as<const double>();
+      lower_args(i);
+      Partition &pf = final_partition(g, pl, C);
       a.Y = nullptr;
       a.tr = pc.tr.as<const double>();
       a.q_cnt1 = c1 ? c1 : any;
@@ -1123,9 +1214,9 @@ void split_dense(ged_graph *g, SplitWs &w, const SplitPlan &pl, int C, const uin
       a.q_even = pl.even ? 1 : 0;
       const int out = c16 ? OUT_COMBINE16 : (pl.c32 && pl.s >= 1) ? OUT_COMBINE32 : OUT_COMBINE;
       if (profile)
-        run_step(g, ps, a, in, out, st, c16 ? 0.75 : pl.s * (pl.c32 ? 0.5 : 1.0) + pl.nlv);
+        run_step(g, pf, a, in, out, st, c16 ? 0.75 : pl.s * (pl.c32 ? 0.5 : 1.0) + pl.nlv);
       else
-        launch_step(ps, a, in, out, st);
+        launch_step(pf, a, in, out, st);
     }
   }
 }
@@ -1201,8 +1292,7 @@ void split_tile_reduce(ged_graph *g, SplitWs &w, const SplitPlan &pl, int C, dou
   w.ws.into(a);
   a.C = C;
   // the partials are laid out by the partition of the combining step
-  launch_reduce(step_partition(g, pl, C, final_in(pl)), a, out, nullptr, nullptr, st,
-                w.ws.scratch());
+  launch_reduce(final_partition(g, pl, C), a, out, nullptr, nullptr, st, w.ws.scratch());
 }
 
 void enqueue_split_tile(ged_graph *g, SplitWs &w, const SplitPlan &pl, int C,
@@ -1365,7 +1455,7 @@ int split_score(ged_graph *g, const int32_t *S, int32_t s_len, double *out) {
           g->omega_lv.p, g->out_host.p, (const void *)st, abits, (const void *)(intptr_t)g->prep.ell,
           (const void *)(intptr_t)cap, (const void *)(uintptr_t)w.wl_cap,
           (const void *)(intptr_t)1 /* split */, (const void *)(intptr_t)pl.lv32,
-          (const void *)(intptr_t)pl.dense2, g->omega2_f.p};
+          (const void *)(intptr_t)pl.dense2, g->omega2_f.p, g->ci_l.p};
       SplitExec &x = g->split_exec[(pl.push3 ? 1 : 0) + (staged ? 2 : 0) + (pl.lv32 ? 4 : 0) +
                                    (pl.dense2 ? 8 : 0)];
       if (x.exec && sig != x.sig) x.drop();

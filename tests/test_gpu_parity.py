@@ -1359,3 +1359,44 @@ def test_score_gathered_level2(ged):
             say(f"[gathered level 2] rmat16 |S|={len(S)}")
             assert rel(gg.score(S, alpha, 1e-2), w) <= REL
     gg.close()
+
+
+@pytest.mark.parametrize("name", ["er_dense", "bipartite", "ba20k", "multi", "keep_order"])
+def test_odd_length_quadratic_form(ged, name):
+    """Odd walk lengths close with a quadratic form over each edge once: single
+    scores and batches (narrow, 16-bit and 64-column tiles) at ell* = 3, 5, 7
+    against the oracle, with lower rows longer than a block (segments and
+    their fix-up), repeated arcs and the caller's vertex order."""
+    g = {"er_dense": lambda: inputs.erdos_renyi(600, 60_000, 3),
+         "bipartite": lambda: inputs.from_edges(
+             4400, np.repeat(np.arange(2200, dtype=np.int32), 2200),
+             2200 + np.tile(np.arange(2200, dtype=np.int32), 2200)),
+         "ba20k": lambda: inputs.barabasi_albert(20_000, 5, 9),
+         "multi": ba_multigraph,
+         "keep_order": lambda: inputs.barabasi_albert(3000, 6, 8)}[name]()
+    gg = ged.GedGraph.from_graph(g, keep_order=name == "keep_order")
+    alpha = 0.2 / g.max_degree
+    hub = int(np.argmax(g.degrees))
+    groups = [inputs.group(g.n, 1, 1), np.array([hub], np.int32), inputs.group(g.n, 40, 2),
+              inputs.group(g.n, g.n // 3, 3), np.arange(g.n, dtype=np.int32)]
+    off = np.concatenate([[0], np.cumsum([len(S) for S in groups])]).astype(np.int64)
+    mem = np.concatenate(groups).astype(np.int32)
+    # the largest eps (a power of ten below the first bound) of each odd length
+    seen = {}
+    for e in range(60):
+        eps = 10.0 ** (3 - 0.25 * e)
+        ell = gg.prepare(alpha, eps)[0]
+        if ell % 2 and 3 <= ell <= 7:
+            seen.setdefault(ell, eps)
+    assert {3, 5} <= set(seen), seen
+    for ell, eps in sorted(seen.items()):
+        say(f"[odd length] {name} n={g.n} nnz={g.nnz} ell={ell}")
+        want = [oracle.score(g, S, alpha, eps)[0] for S in groups]
+        for S, w in zip(groups, want):
+            assert rel(gg.score(S, alpha, eps), w) <= REL, (ell, len(S))
+        for tile in (2, 4, 64):
+            gg.set_batch_tile(tile)
+            gg.set_batch_row_cut(2)
+            s = gg.score_batch(off, mem, alpha, eps)
+            assert max(rel(x, w) for x, w in zip(s, want)) <= REL, (ell, tile)
+    gg.close()
