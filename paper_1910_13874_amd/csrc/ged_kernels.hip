@@ -91,15 +91,15 @@ __device__ __forceinline__ uint4 load_quad16(const StepArgs &a, int u, int k) {
 
 // The packed 8 bytes of columns 4k .. 4k+3 of row u as staged in LDS: the
 // row's four 16-bit counts; for a row below the hub cut its 32-bit counts,
-// loaded with the other gathers, each staged as itself when it fits 16 bits
-// (most do: the cut is a bound) and as kC16Hub when it does not.
+// each staged as itself when it fits 16 bits (most do: the cut is a bound)
+// and as kC16Hub when it does not.
 template <int C>
 __device__ __forceinline__ uint2 load_pk16(const StepArgs &a, int u, int k) {
   uint2 p = *reinterpret_cast<const uint2 *>(a.Xc16 + (size_t)u * C + 4 * k);
   if (u < a.hub) {
     const uint4 h = *reinterpret_cast<const uint4 *>(a.Xc32 + (size_t)u * C + 4 * k);
-    auto m = [](uint32_t x) -> uint32_t { return x > kC16Max ? kC16Hub : x; };
-    p = make_uint2(m(h.x) | (m(h.y) << 16), m(h.z) | (m(h.w) << 16));
+    p = make_uint2(min(h.x, kC16Hub) | (min(h.y, kC16Hub) << 16),
+                   min(h.z, kC16Hub) | (min(h.w, kC16Hub) << 16));
   }
   return p;
 }
@@ -428,13 +428,201 @@ __device__ __forceinline__ void block_colsum_quads(const double (&v)[4], double 
   if (t < C) out[t] = (red[t] + red[C + t]) + (red[2 * C + t] + red[3 * C + t]);
 }
 
+// ---- Rows of a 16-bit step, NC columns per lane.
+//
+// These steps (64 columns: an arc is one 128-byte line) are bound by vector
+// issue, not by the gathers, when each lane sums one column: a 16-bit LDS
+// read, its address, the test for kC16Hub and 64-bit bookkeeping per (arc,
+// column) kept the SIMDs 99 % (level 3) and 105 % (combining step) busy
+// (SQ_ACTIVE_INST_VALU over SQ_BUSY_CU_CYCLES, BA n = 2e6).  Here a lane reads
+// NC columns of an arc at once and adds their halves to 32-bit partials (at
+// most 2048 arcs of 16-bit values), and the running packed maximum tells
+// whether the row met kC16Hub at all; the epilogue's streams are read and
+// written NC columns at a time.  Four columns for the stored levels; two for
+// the combining step, whose FP64 epilogue on four would leave its eight waves
+// per SIMD no registers (36 bytes spilled, 1.8 ms instead of 1.05).  BA
+// n = 2e6, m = 8, 64 columns: level 3 1,241 -> 1,088 us beside the next
+// tile's pushes (680 us alone), combining step 1,050 -> 922 us, or at odd
+// ell* over the lower arcs 1,024 groups 33.0 -> 27.9 ms.
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+
+__device__ __forceinline__ uint32_t pk_max16(uint32_t a, uint32_t b) {
+  const u16x2 m = __builtin_elementwise_max(__builtin_bit_cast(u16x2, a),
+                                            __builtin_bit_cast(u16x2, b));
+  return __builtin_bit_cast(uint32_t, m);
+}
+
+__device__ __forceinline__ uint32_t half16(uint32_t x, int i) {
+  return (x >> (16 * (i & 1))) & 0xffffu;
+}
+
+// Columns a lane of quad_rows takes.
+template <int OUT>
+constexpr int quad_cols() {
+  return OUT == OUT_COMBINE16 ? 2 : 4;
+}
+
+// The combination's inputs for row v, columns 2k and 2k + 1 (CombineIn, 16-bit
+// level-2 rows): level 1, the packed level 2, the 16-bit copy of a single
+// stored level, sum t_c, t_a (t_b).  Rows below the cut and further stored
+// levels are read when they are used.
+template <int C>
+struct CombinePair {
+  u32x2 c1;
+  uint32_t pk, h0;
+  double trv, ta;
+  __device__ __forceinline__ void load(const StepArgs &a, int v, int k) {
+    const size_t o = (size_t)v * C + 2 * k;
+    c1 = __builtin_nontemporal_load(
+        reinterpret_cast<const u32x2 *>(static_cast<const uint32_t *>(a.q_cnt1) + o));
+    pk = __builtin_nontemporal_load(reinterpret_cast<const uint32_t *>(a.q_pk2 + o));
+    // without a single stored level its copy does not exist: entry 0
+    h0 = __builtin_nontemporal_load(
+        reinterpret_cast<const uint32_t *>(a.Xc16 + (a.q_nlv == 1 ? o : 0)));
+    trv = a.tr[v];
+    ta = a.inj[v];
+  }
+  // The row's share of column 2k + i, given the gathered sum.
+  __device__ __forceinline__ double share(const StepArgs &a, int v, int k, int i, double sum,
+                                          bool member) const {
+    const size_t o = (size_t)v * C + 2 * k + i;
+    const uint32_t *lv = static_cast<const uint32_t *>(a.q_lv);
+    uint32_t c2 = half16(pk, i);
+    if (v < a.q_hub2) c2 = static_cast<const uint32_t *>(a.q_cnt2)[o];
+    double top = a.q_s2 * (double)c2;
+    double q = a.q_s1 * (double)c1[i] + top;
+    if (a.q_nlv == 1) {
+      uint32_t x = half16(h0, i);
+      if (x == kC16Hub) x = lv[o];  // marked: its 32-bit count
+      top = a.q_slv * (double)x;
+      q += top;
+    } else {
+      double w = a.q_slv;
+      for (int l = 0; l < a.q_nlv; ++l, w *= a.q_alpha) {
+        top = w * (double)lv[(size_t)l * a.n * C + o];
+        q += top;
+      }
+    }
+    const double y = a.alpha * sum;
+    return a.q_quad ? combine_quad(q, top, y, trv, ta, member)
+                    : combine_fin(a, q, member ? ta : y, trv, ta, member);
+  }
+};
+
+// Phase 2 of a 16-bit row block (OUT_TILE32, OUT_TILE32H, OUT_COMBINE16).
+// vals holds the block's arcs, C halves each; of the LA = C/NC lanes per arc,
+// lane t takes columns NC*k .. NC*k + NC - 1, k = t % LA, of row slot
+// t / (LA * tpr), striding the row's arcs by tpr: the lanes of an arc read
+// consecutive words (no bank conflicts).  pf: the combination's inputs of the
+// first row.  cs receives the lane's column sums (combining step).
+template <int C, int OUT, class TW>
+__device__ __forceinline__ void quad_rows(const StepArgs &a, const uint32_t *vals, const int *rps,
+                                          const TW *tmw, int r0, int nrows, const int *src,
+                                          int tpr, CombinePair<C> &pf,
+                                          double (&cs)[quad_cols<OUT>()]) {
+  constexpr int NC = quad_cols<OUT>(), LA = C / NC, NW = NC / 2;
+  using V = typename std::conditional<NC == 4, u32x2, uint32_t>::type;  // NC halves
+  const V *vv = reinterpret_cast<const V *>(vals);
+  auto word = [](V x, int w) -> uint32_t {
+    if constexpr (NC == 4)
+      return x[w];
+    else
+      return x;
+  };
+  const int t = threadIdx.x;
+  const int k = t & (LA - 1), s = (t / LA) & (tpr - 1);
+  const int rstep = kBlock / LA / tpr;
+  for (int rl = t / LA / tpr; rl < nrows; rl += rstep) {
+    const int j0 = rps[rl], j1 = rps[rl + 1];
+    const int r = r0 + rl;
+    // a later row's inputs: requested ahead of its sums
+    if (OUT == OUT_COMBINE16 && rl >= rstep) pf.load(a, r, k);
+    uint32_t q[NC] = {}, mx[NW] = {};
+    auto add = [&](V x) {
+#pragma unroll
+      for (int i = 0; i < NC; ++i) q[i] += half16(word(x, i / 2), i);
+#pragma unroll
+      for (int w = 0; w < NW; ++w) mx[w] = pk_max16(mx[w], word(x, w));
+    };
+    int j = j0 + s;
+    for (; j + 3 * tpr < j1; j += 4 * tpr) {  // four LDS reads in flight
+      const V x0 = vv[j * LA + k], x1 = vv[(j + tpr) * LA + k];
+      const V x2 = vv[(j + 2 * tpr) * LA + k], x3 = vv[(j + 3 * tpr) * LA + k];
+      add(x0);
+      add(x1);
+      add(x2);
+      add(x3);
+    }
+    for (; j < j1; j += tpr) add(vv[j * LA + k]);
+    for (int off = LA; off < LA * tpr; off <<= 1) {
+#pragma unroll
+      for (int i = 0; i < NC; ++i) q[i] += __shfl_xor(q[i], off, 64);
+#pragma unroll
+      for (int w = 0; w < NW; ++w) mx[w] = pk_max16(mx[w], __shfl_xor(mx[w], off, 64));
+    }
+    // Column i's exact sum: marked values (the row's lanes agree on mx) take
+    // the 32-bit counts at their sources in place of kC16Hub.  With a cut
+    // they sit below it, and those sources, the smallest ids, come first in
+    // the row.
+    auto total = [&](int i) -> double {
+      double d = (double)q[i];
+      if (half16(mx[i / 2], i) == kC16Hub) {
+        double e = 0.0;
+        for (int jj = j0 + s; jj < j1; jj += tpr) {
+          const int u = src[jj];
+          if (a.hub > 0 && u >= a.hub) break;
+          if (half16(word(vv[jj * LA + k], i / 2), i) == kC16Hub)
+            e += (double)a.Xc32[(size_t)u * C + NC * k + i] - (double)kC16Hub;
+        }
+        for (int off = LA; off < LA * tpr; off <<= 1) e += __shfl_xor(e, off, 64);
+        d += e;  // exact integers
+      }
+      return d;
+    };
+    const uint32_t mem = (uint32_t)(tmw[rl] >> (NC * k)) & ((1u << NC) - 1);
+    if constexpr (OUT == OUT_COMBINE16) {
+#pragma unroll
+      for (int i = 0; i < NC; ++i) {
+        const double sum = total(i);
+        if (s == 0) cs[i] += pf.share(a, r, k, i, sum, (mem >> i) & 1u);
+      }
+    } else {
+      // exact counts (alpha = 1); members take the level's omega
+      const size_t o = (size_t)r * C + NC * k;
+      u32x4 y;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) y[i] = (uint32_t)total(i);
+      if (s != 0) continue;
+      if (mem) {
+        const uint32_t w = (uint32_t)a.inj[r];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if ((mem >> i) & 1u) y[i] = w;
+      }
+      if constexpr (OUT == OUT_TILE32H) {
+        const uint32_t big = max(max(y[0], y[1]), max(y[2], y[3]));
+        uint32_t h[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) h[i] = min(y[i], kC16Hub);
+        const u32x2 p = {h[0] | (h[1] << 16), h[2] | (h[3] << 16)};
+        __builtin_nontemporal_store(p, reinterpret_cast<u32x2 *>(a.Y16 + o));
+        if (!a.y32_marked || big > kC16Max)  // a marked count takes its neighbours along
+          __builtin_nontemporal_store(y, reinterpret_cast<u32x4 *>(a.Y32 + o));
+      } else {
+        __builtin_nontemporal_store(y, reinterpret_cast<u32x4 *>(a.Y32 + o));
+      }
+    }
+  }
+}
+
 // Waves per SIMD the register allocation must allow (1: the compiler's
-// choice).  The combining steps over 16-bit counts would take 68-70 VGPRs,
-// i.e. seven waves; held to eight (64 VGPRs, no spill) they ran the 4,096-group
-// BA-2M batch 7 % faster, the LDS of eight resident blocks of four waves
-// fitting a CU.  The bound is not set on the other steps: those within 64
-// VGPRs already are scheduled differently under it (the FP64 gain step lost
-// 2 %), and the larger ones would spill.
+// choice).  The combining steps over 16-bit counts (57-62 VGPRs) are held to
+// eight, the LDS of eight resident blocks of four waves fitting a CU; at
+// seven they ran 7 % slower.  The bound is not set on the other steps: those
+// within 64 VGPRs already are scheduled differently under it (the FP64 gain
+// step lost 2 %), and the larger ones would spill.
 template <int C, int IN, int OUT, bool WGT>
 constexpr int step_waves() {
   return !WGT && IN == IN_CNT16 && OUT == OUT_COMBINE16 ? 8 : 1;
@@ -452,6 +640,8 @@ void k_step(StepArgs a, const int4 *__restrict__ blocks,
   // NP: 32-bit input gathered as column pairs; a gather unit is 8 bytes
   // either way (one FP64 value or two 32-bit values), CU units per arc
   constexpr bool NP = narrow_gather(C, IN, WGT);
+  // the column sums of exact count levels are never reduced
+  constexpr bool NOSUM = OutTraits<OUT>::store32 || OUT == OUT_ZERO32 || OUT == OUT_GAIN32D;
   // Q4: 16-bit inputs (IN_CNT16) gathered as 8-byte units of four columns
   // and staged as 16-bit values (partition_quad: kLdsDoubles / (C/4) arcs)
   constexpr bool Q4 = IN == IN_CNT16 && C >= 4 && !WGT;
@@ -526,11 +716,20 @@ void k_step(StepArgs a, const int4 *__restrict__ blocks,
     }
     // The combining epilogue's row data for this thread's first (row, column)
     // pair of phase 2, loaded now so it arrives with the gathers.
-    int tpr = (kBlock / C < 64) ? kBlock / C : 64;
-    while (tpr > 1 && nrows * C * tpr > kBlock) tpr >>= 1;
-    const int rl0 = (t / tpr) / C;
+    // phase 2: tpr lanes per (row, column), or per row and columns of a lane
+    // of quad_rows (QR), whose lanes of one row stay within a wavefront
+    constexpr bool QR = Q4 && (OUT == OUT_COMBINE16 || OUT == OUT_TILE32 || OUT == OUT_TILE32H);
+    constexpr int PC = QR ? C / quad_cols<OUT>() : C;
+    constexpr int TM0 = QR ? 64 / PC : kBlock / C;
+    int tpr = TM0 < 64 ? TM0 : 64;
+    while (tpr > 1 && nrows * PC * tpr > kBlock) tpr >>= 1;
+    const int rl0 = (t / tpr) / PC;
     CombineFor<C, OUT> pf;
-    if constexpr (CB) pf.load(a, r0 + min(rl0, nrows - 1), (t / tpr) & (C - 1));
+    CombinePair<C> pq;
+    if constexpr (QR && CB)
+      pq.load(a, r0 + min(rl0, nrows - 1), t & (PC - 1));
+    else if constexpr (CB)
+      pf.load(a, r0 + min(rl0, nrows - 1), (t / tpr) & (C - 1));
     if constexpr (HC) {
       if (a.hc_rows > 0) {  // uniform: the copy of the first rows is in place
 #pragma unroll
@@ -543,7 +742,7 @@ void k_step(StepArgs a, const int4 *__restrict__ blocks,
 #pragma unroll
     for (int q = 0; q < PT; ++q) {
       if constexpr (Q4) {
-        v2[q] = load_pk16<C>(a, u[q], (t + q * kBlock) & (GU - 1));
+        v2[q] = *reinterpret_cast<const uint2 *>(a.Xc16 + (size_t)u[q] * C + 4 * (t & (GU - 1)));
       } else if constexpr (NP) {
         v2[q] = *reinterpret_cast<const uint2 *>(a.Xc32 + (size_t)u[q] * C +
                                                  2 * ((t + q * kBlock) & (CU - 1)));
@@ -557,6 +756,14 @@ void k_step(StepArgs a, const int4 *__restrict__ blocks,
       } else {
         v[q] = load_in<C, IN>(a, u[q], (t + q * kBlock) & (C - 1));
         if constexpr (WGT) v[q] *= a.w[min(jlo + (t + q * kBlock) / C, jmax)];
+      }
+    }
+    if constexpr (Q4) {
+      // rows below the cut: their 32-bit counts, after every packed load
+      if (a.hub > 0) {
+#pragma unroll
+        for (int q = 0; q < PT; ++q)
+          if (u[q] < a.hub) v2[q] = load_pk16<C>(a, u[q], t & (GU - 1));
       }
     }
 #pragma unroll
@@ -573,14 +780,27 @@ void k_step(StepArgs a, const int4 *__restrict__ blocks,
 #pragma unroll
     for (int q = 0; q < PT; ++q) {
       const int f = t + q * kBlock;
-      if (f < tot) {
-        if constexpr (NP || Q4)
+      if constexpr (Q4) {
+        // every slot f < LV exists; those past the block's units are not read
+        reinterpret_cast<uint2 *>(vals)[f] = v2[q];
+      } else if (f < tot) {
+        if constexpr (NP)
           reinterpret_cast<uint2 *>(vals)[f] = v2[q];
         else
           vals[f] = (SV)v[q];
       }
     }
     __syncthreads();
+    if constexpr (QR) {
+      double cs[quad_cols<OUT>()] = {};
+      quad_rows<C, OUT, TW>(a, reinterpret_cast<const uint32_t *>(vals), rps, tmw, r0, nrows,
+                            a.ci + p0, tpr, pq, cs);
+      if constexpr (CB) {
+        __syncthreads();  // red shares the staged values' storage
+        block_colsum_pairs<C>(cs[0], cs[1], red, a.blk_part + (size_t)b * C);
+      }
+      return;
+    }
     // Phase 2: tpr lanes per (row, column), as many as the row count allows.
     const int s = t & (tpr - 1);
     const int pair = t / tpr;
@@ -657,8 +877,10 @@ void k_step(StepArgs a, const int4 *__restrict__ blocks,
         }
       }
     }
-    __syncthreads();  // red shares the staged values' storage
-    block_colsum<C>(colsum, tpr, red, a.blk_part + (size_t)b * C, a.accum);
+    if constexpr (!NOSUM) {
+      __syncthreads();  // red shares the staged values' storage
+      block_colsum<C>(colsum, tpr, red, a.blk_part + (size_t)b * C, a.accum);
+    }
   } else if (a.bk_ci != nullptr) {
     // Bucket block: pieces [s0, s0 + np) of long rows, all of whose sources
     // lie in one or two adjacent buckets; the same two phases as a row block
