@@ -757,7 +757,7 @@ void split_tile_push(ged_graph *g, SplitWs &w, const SplitPlan &pl, int C, const
                      uint64_t *tmask, hipStream_t st, bool set_tmask = true);
 void split_tile_reduce(ged_graph *g, SplitWs &w, const SplitPlan &pl, int C, double *out,
                        hipStream_t st);
-// fill: zero the count levels with a dense fill instead of replaying the
+// fill: zero count level 2 with a dense fill instead of replaying the
 // pushes (split_clear_by_fill decides from the tile's estimated push volume).
 void split_tile_clear(ged_graph *g, SplitWs &w, const SplitPlan &pl, int C, const int64_t *offs,
                       const int *mem, const int *mcol, int g0, int nc, int64_t tile_members,

@@ -254,8 +254,11 @@ __device__ __forceinline__ void clear_entry(const int *__restrict__ rp,
 // stores zeros instead.  NEXT: wl_next is used (the adds return the old
 // count); otherwise the adds return nothing and the wave does not wait.  The
 // level-2 push also fixes the member rows (fx): it neither reads nor writes
-// them, and the member pushes before it have finished.
-template <class CT, bool CLEAR, bool NEXT>
+// them, and the member pushes before it have finished.  CHECK false: the
+// adds go to member rows too (their sums stay within omega_2) and the caller
+// fixes them after the launch; a tile's push then makes one random access per
+// arc instead of two, beside a dense step that its accesses slow down.
+template <class CT, bool CLEAR, bool NEXT, bool CHECK = true>
 __global__ __launch_bounds__(kBlock) void k_push_wl(const int *__restrict__ rp,
                                                     const int *__restrict__ ci, int C,
                                                     const CT *src, CT *dst, const uint64_t *wl,
@@ -287,7 +290,7 @@ __global__ __launch_bounds__(kBlock) void k_push_wl(const int *__restrict__ rp,
     for (int k = 0; k < U; ++k) x[k] = j0 + 64 * k < j1 ? ci[j0 + 64 * k] : -1;
     bool out[U];
 #pragma unroll
-    for (int k = 0; k < U; ++k) out[k] = x[k] >= 0 && !((tmask[x[k]] >> c) & 1ull);
+    for (int k = 0; k < U; ++k) out[k] = x[k] >= 0 && (!CHECK || !((tmask[x[k]] >> c) & 1ull));
     const CT v = src[(size_t)y * C + c];
     if (!NEXT) {
 #pragma unroll
@@ -999,12 +1002,20 @@ static void push_phase(ged_graph *g, SplitWs &w, const SplitPlan &pl, int C, con
       hipLaunchKernelGGL((k_push_wl<CT, false, true>), dim3(w.wl_blocks), dim3(kBlock), 0, st, rp,
                          ci, C, c1, c2, w.wl.as<const uint64_t>(), w.wl_n.as<const unsigned>(),
                          w.wl_cap, tmask, wl3, wl3_n, w.wl3_cap, fx, h16);
-    else
+    else if (C == 1)
       hipLaunchKernelGGL((k_push_wl<CT, false, false>), dim3(w.wl_blocks), dim3(kBlock), 0, st,
                          rp, ci, C, c1, c2, w.wl.as<const uint64_t>(),
                          w.wl_n.as<const unsigned>(), w.wl_cap, tmask, (uint64_t *)nullptr,
                          (unsigned *)nullptr, 0u, fx, h16);
-  } else {
+    else
+      hipLaunchKernelGGL((k_push_wl<CT, false, false, false>), dim3(w.wl_blocks), dim3(kBlock), 0,
+                         st, rp, ci, C, c1, c2, w.wl.as<const uint64_t>(),
+                         w.wl_n.as<const unsigned>(), w.wl_cap, tmask, (uint64_t *)nullptr,
+                         (unsigned *)nullptr, 0u, MemberFix<CT>(), h16);
+  }
+  // member rows after an unchecked push, or where there was none
+  if (!c2 || (!wl3 && C > 1)) {
+    GED_HIP(hipGetLastError());
     hipLaunchKernelGGL(k_fix_members<CT>, dim3(grid_for((tile_members + kBlock - 1) / kBlock, 256)),
                        dim3(kBlock), 0, st, fx);
   }
@@ -1021,10 +1032,10 @@ static void push_phase(ged_graph *g, SplitWs &w, const SplitPlan &pl, int C, con
 template <class CT>
 static void clear_phase(ged_graph *g, SplitWs &w, const SplitPlan &pl, int C,
                         const int64_t *offs, const int *mem, const int *mcol, int g0, int nc,
-                        int mgrid, uint64_t *tmask, hipStream_t st) {
+                        int mgrid, uint64_t *tmask, bool level2_zero, hipStream_t st) {
   const int *rp = g->rp.as<const int>(), *ci = g->ci.as<const int>();
   CT *c1 = w.cnt1.as<CT>();
-  CT *c2 = pl.s >= 2 ? w.cnt2.as<CT>() : nullptr;
+  CT *c2 = pl.s >= 2 && !level2_zero ? w.cnt2.as<CT>() : nullptr;
   CT *l3 = pl.push3 ? w.lv.as<CT>() : nullptr;
   const int h16 = sizeof(CT) == 4 ? pl.c16_hub : -1;
   if (l3) {  // level-2 and pushed level-3 targets in one launch
@@ -1041,8 +1052,8 @@ static void clear_phase(ged_graph *g, SplitWs &w, const SplitPlan &pl, int C,
   }
   hipLaunchKernelGGL(k_clear_members<CT>, dim3(mgrid), dim3(kBlock), 0, st, rp, ci, offs, mem,
                      mcol, g0, nc, C, c1, c2, l3, reinterpret_cast<unsigned long long *>(tmask),
-                     c2 ? w.wl_n.as<unsigned>() : nullptr, l3 ? w.wl3_n.as<unsigned>() : nullptr,
-                     h16);
+                     pl.s >= 2 ? w.wl_n.as<unsigned>() : nullptr,
+                     l3 ? w.wl3_n.as<unsigned>() : nullptr, h16);
   GED_HIP(hipGetLastError());
 }
 
@@ -1235,14 +1246,14 @@ void split_tile_push(ged_graph *g, SplitWs &w, const SplitPlan &pl, int C, const
   }
 }
 
-// Replaying a push stores one zero per arc it wrote along, each to its own
-// cache line (about 64 bytes of traffic); a fill writes the count levels of
-// the tile's width once.  Replay while that is cheaper.
+// Replaying a level-2 push stores one zero per arc it wrote along, each to
+// its own cache line (about 64 bytes of traffic); a fill writes level 2 of the
+// tile's width once, in whole lines (level 1 is replayed from the members
+// either way: its writes are their arcs).  Replay while that is cheaper.
 bool split_clear_by_fill(const ged_graph *g, const SplitPlan &pl, int C, double push2_arcs) {
   if (pl.s < 2 || pl.push3) return false;
-  const double cb = pl.c32 ? 4.0 : 8.0;
-  const double cb2 = pl.c16_hub >= 0 ? 2.0 : cb;  // level 2 in the 16-bit layout
-  return push2_arcs * 64.0 > (double)g->n * C * (cb + cb2);
+  const double cb2 = pl.c16_hub >= 0 ? 2.0 : pl.c32 ? 4.0 : 8.0;
+  return push2_arcs * 64.0 > (double)g->n * C * cb2;
 }
 
 // A push adds one scattered 4-byte atomic per arc: measured 20 G adds/s on
@@ -1267,20 +1278,18 @@ void split_tile_clear(ged_graph *g, SplitWs &w, const SplitPlan &pl, int C, cons
                       uint64_t *tmask, hipStream_t st, bool fill) {
   const int mgrid = grid_for(tile_members, kPushGrid);
   // a gathered level 2 has no worklist to replay
-  if ((fill || pl.dense2) && pl.s >= 2 && !pl.push3) {
-    // the two count levels of this width, the members' column bits and the
-    // worklist length: everything the pushes wrote
+  const bool fill2 = (fill || pl.dense2) && pl.s >= 2 && !pl.push3;
+  if (fill2) {
     const size_t words = (size_t)g->n * C * (pl.c32 ? 1 : 2);
-    launch_fill_i32(w.cnt1.as<int>(), 0, words, st);
     launch_fill_i32(w.cnt2.as<int>(), 0,
                     pl.c16_hub >= 0 ? (c16_bytes(g->n, pl.c16_hub, C) + 3) / 4 : words, st);
-    launch_fill_i32(w.wl_n.as<int>(), 0, 1, st);
-    launch_tmask_set(tmask, offs, mem, g0, nc, 0, st);
-  } else if (pl.s >= 1) {  // clears the members' tmask bits too
+  }
+  if (pl.s >= 1) {  // clears the members' tmask bits and the worklist lengths too
     if (pl.c32)
-      clear_phase<unsigned>(g, w, pl, C, offs, mem, mcol, g0, nc, mgrid, tmask, st);
+      clear_phase<unsigned>(g, w, pl, C, offs, mem, mcol, g0, nc, mgrid, tmask, fill2, st);
     else
-      clear_phase<unsigned long long>(g, w, pl, C, offs, mem, mcol, g0, nc, mgrid, tmask, st);
+      clear_phase<unsigned long long>(g, w, pl, C, offs, mem, mcol, g0, nc, mgrid, tmask, fill2,
+                                      st);
   } else {
     launch_tmask_set(tmask, offs, mem, g0, nc, 0, st);
   }
