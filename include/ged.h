@@ -167,6 +167,9 @@ int ged_score(ged_graph *g, const int32_t *S, int32_t s_len, double alpha, doubl
  * members[offsets[j] .. offsets[j+1])), all at the shared ell*.  Groups run as
  * columns of a masked sparse-matrix x dense-matrix product, in tiles whose
  * width is chosen per graph by an autotuner; out_scores float64[n_groups].
+ * On graphs of at most 18,000 vertices and 128 K arcs each group runs in one
+ * workgroup instead (no tile; ged_batch_tile then reports a nominal 64),
+ * unless a tile width, a row-split divisor or a 16-bit cut was set.
  * Each result equals ged_score on the same group to ~1e-12 relative.
  */
 int ged_score_batch(ged_graph *g, const int64_t *offsets, const int32_t *members,

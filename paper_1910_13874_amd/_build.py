@@ -21,6 +21,7 @@ HIP_SOURCES = [
     "ged_greedy.hip",
     "ged_server.hip",
     "ged_noalloc.hip",
+    "ged_small.hip",
 ]
 
 HIP_FLAGS = [

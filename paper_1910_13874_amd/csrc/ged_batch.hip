@@ -230,6 +230,36 @@ static void enqueue_batch(ged_graph *g, BatchWs &b, int G, int C, hipStream_t st
   }
 }
 
+// A batch on a small graph (ged_small.hip): the groups are written to coherent
+// host memory, which the one kernel reads and writes the scores back to.
+static int small_batch(ged_graph *g, const int64_t *offsets, const int32_t *members, int32_t G,
+                       double *out) {
+  if (g->batch_tile == 0) {  // what the getters report; no tile is formed
+    g->batch_tile = 64;
+    g->batch_cut_div = 1;
+    g->tile_nominal = true;
+  }
+  g->c16_used = -1;
+  std::vector<int> mem;
+  mem.reserve((size_t)offsets[G]);
+  const size_t ob = sizeof(int64_t) * ((size_t)G + 1), sb = sizeof(double) * (size_t)G;
+  g->small_in.ensure(ob + sb + sizeof(int) * (size_t)std::max<int64_t>(offsets[G], g->n),
+                     hipHostMallocCoherent);
+  int64_t *ho = g->small_in.as<int64_t>();
+  double *hs = reinterpret_cast<double *>(ho + G + 1);
+  int *hm = reinterpret_cast<int *>(hs + G);
+  for (int j = 0; j < G; ++j) {
+    ho[j] = (int64_t)mem.size();
+    map_group(g, members + offsets[j], offsets[j + 1] - offsets[j], mem);
+  }
+  ho[G] = (int64_t)mem.size();
+  std::memcpy(hm, mem.data(), sizeof(int) * mem.size());
+  small_scores(g, ho, hm, G, hs, g->stream);
+  GED_HIP(hipStreamSynchronize(g->stream));
+  std::memcpy(out, hs, sb);
+  return GED_OK;
+}
+
 int score_batch(ged_graph *g, const int64_t *offsets, const int32_t *members, int32_t G,
                 double alpha, double eps, double *out) {
   if (G < 0 || (G > 0 && (!offsets || !out))) return fail(GED_ERR_ARG, "bad batch arguments");
@@ -244,6 +274,15 @@ int score_batch(ged_graph *g, const int64_t *offsets, const int32_t *members, in
   int rc = prepare(g, alpha, eps);
   if (rc) return rc;
   hipStream_t st = g->stream;
+  // one workgroup per group where the graph is small, unless the caller fixed
+  // the tiles or profiles their steps
+  if (!g->prof.on && !g->tile_fixed && !g->cut_fixed && g->count16 == 0 && small_batch_ok(g))
+    return small_batch(g, offsets, members, G, out);
+  if (g->tile_nominal) {
+    if (!g->tile_fixed) g->batch_tile = 0;
+    if (!g->cut_fixed) g->batch_cut_div = 0;
+    g->tile_nominal = false;
+  }
   BatchWs &b = batch_ws(g);
   const int64_t n = g->n;
   b.tmask.ensure(sizeof(uint64_t) * (size_t)n);
@@ -261,8 +300,7 @@ int score_batch(ged_graph *g, const int64_t *offsets, const int32_t *members, in
   pl.cut_div = g->batch_cut_div;
   if (split) pl.c16_hub = split_c16_hub(g, pl, C, st);
   g->c16_used = pl.c16_hub;
-  Partition &p = partition(g, C, false, g->batch_cut_div);
-  b.ws.fit(p);
+  b.ws.fit(partition(g, C, false, g->batch_cut_div));
   // internal ids, duplicates inside a group dropped; column of every member
   std::vector<int64_t> &hoff = b.h_offsets;
   std::vector<int> &hmem = b.h_members;
@@ -462,7 +500,11 @@ extern "C" int ged_set_batch_tile(ged_graph *g, int32_t tile) {
     return fail(GED_ERR_ARG, "tile must be 0 (autotune) or a power of two <= 64");
   std::lock_guard<std::recursive_mutex> lk(g->mu);
   g->batch_tile = tile;
-  if (tile == 0) g->batch_cut_div = 0;
+  g->tile_fixed = tile != 0;
+  if (tile == 0) {
+    g->batch_cut_div = 0;
+    g->cut_fixed = false;
+  }
   return GED_OK;
 }
 
@@ -488,5 +530,6 @@ extern "C" int ged_set_batch_row_cut(ged_graph *g, int32_t cut_div) {
     return fail(GED_ERR_ARG, "cut_div must be 0 (autotune), 1, 2 or 4");
   std::lock_guard<std::recursive_mutex> lk(g->mu);
   g->batch_cut_div = cut_div;
+  g->cut_fixed = cut_div != 0;
   return GED_OK;
 }

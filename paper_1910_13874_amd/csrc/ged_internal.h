@@ -510,6 +510,8 @@ struct SplitExec {
   void drop();
 };
 
+struct SmallGraph;  // slices of a small graph (ged_small.hip)
+
 struct Profiler {
   bool on = false;
   struct Rec {
@@ -592,6 +594,10 @@ struct ged_graph {
   // batched scoring: tile width and row-split threshold divisor (0 = autotune)
   int32_t batch_tile = 0;
   int32_t batch_cut_div = 0;
+  // set by the caller (not by the autotuner): batches run in tiles
+  bool tile_fixed = false, cut_fixed = false;
+  bool tile_nominal = false;  // reported after a batch that formed no tile
+  std::shared_ptr<ged::SmallGraph> small;  // null until first asked for
   // greedy candidate batch width (0 = the library's choice)
   int32_t greedy_width = 0;
   // 16-bit level-2 counts in batch tiles: 0 the library's choice, -1 off,
@@ -635,6 +641,7 @@ struct ged_graph {
   bool split_tmask_ready = false;
   ged::DBuf split_in;           // int64 offsets[2], int members[cap], int mcol[cap]
   ged::HBuf split_in_host;
+  ged::HBuf small_in;           // a small graph's group: offsets {0, len}, members
   int split_cap = 0;
   // profiling
   ged::Profiler prof;
@@ -779,6 +786,25 @@ void enqueue_split_tile(ged_graph *g, SplitWs &w, const SplitPlan &pl, int C,
 // returns the sum of the members' degrees.
 int64_t map_group(ged_graph *g, const int32_t *S, int64_t len, std::vector<int> &out);
 int split_score(ged_graph *g, const int32_t *S, int32_t s_len, double *out);
+
+// Small graphs (ged_small.hip): a whole chain per workgroup, in LDS.  Sources
+// are 16-bit ids and one vertex vector takes at most the CU's LDS.  A batch
+// pays up to 128 K arcs (n = 10^4, 80 K arcs, 256 groups: 700 us in tiles, 150
+// us so; below that the tile path costs a launch chain whatever its size).
+// A single group, one workgroup on one CU, up to 40 K (a level of 80 K arcs
+// takes it 6 us, a step 4 to 5).
+constexpr int64_t kSmallVertices = 18000;
+constexpr int64_t kSmallBatchArcs = 128 << 10;
+constexpr int64_t kSmallScoreArcs = 40 << 10;
+bool small_batch_ok(ged_graph *g);
+bool small_score_ok(ged_graph *g);
+// Scores of groups (members mem[offs[g] .. offs[g+1]), internal ids; device
+// or coherent host memory) to out[groups], for the prepared (alpha, eps).
+// n_inline >= 0: one group, whose n_inline <= kSmallInline members mem (host)
+// travel as kernel arguments.
+constexpr int kSmallInline = 64;
+void small_scores(ged_graph *g, const int64_t *offs, const int *mem, int groups, double *out,
+                  hipStream_t st, int n_inline = -1);
 
 // Run fn, translating HipError into a status code + message.
 template <class F>

@@ -903,7 +903,8 @@ void split_fit(ged_graph *g, SplitWs &w, const SplitPlan &pl, int C, size_t wl_n
   const bool dirty = !w.zero;
   if (!counts_only) {
     w.ws.fit(partition(g, C, false, pl.cut_div));
-    if (pl.s >= 1 && pl.c32) w.ws.fit(step_partition(g, pl, C, IN_CNT32));
+    // every partition split_dense asks for, built before any capture
+    w.ws.fit(step_partition(g, pl, C, IN_CNT32));
     if (pl.c16_hub >= 0) w.ws.fit(step_partition(g, pl, C, IN_CNT16));
     w.ws.fit(final_partition(g, pl, C));
   }
@@ -961,7 +962,7 @@ void split_fit(ged_graph *g, SplitWs &w, const SplitPlan &pl, int C, size_t wl_n
 // narrower tile use the first n * C entries of the same buffers.
 void split_fit_width(ged_graph *g, SplitWs &w, const SplitPlan &pl, int C) {
   w.ws.fit(partition(g, C, false, pl.cut_div));
-  if (pl.s >= 1 && pl.c32) w.ws.fit(step_partition(g, pl, C, IN_CNT32));
+  w.ws.fit(step_partition(g, pl, C, IN_CNT32));
   if (pl.c16_hub >= 0) w.ws.fit(step_partition(g, pl, C, IN_CNT16));
   w.ws.fit(final_partition(g, pl, C));
 }

@@ -1400,3 +1400,56 @@ def test_odd_length_quadratic_form(ged, name):
             s = gg.score_batch(off, mem, alpha, eps)
             assert max(rel(x, w) for x, w in zip(s, want)) <= REL, (ell, tile)
     gg.close()
+
+
+def _random_graph(n, m, seed, directed=False):
+    r = inputs.uniform_ints(2 * m, n, seed)
+    return inputs.from_edges(n, r[0::2], r[1::2], symmetrize=not directed)
+
+
+@pytest.mark.parametrize("n,m,kind", [
+    (1, 0, "plain"), (2, 1, "plain"), (63, 100, "plain"), (64, 64 * 16, "plain"),
+    (65, 2000, "weighted"), (1023, 3000, "directed"), (1025, 9000, "plain"),
+    (2049, 16000, "weighted"), (4097, 16300, "directed"), (6145, 40000, "plain"),
+    (10_000, 60_000, "directed"), (10_241, 60_000, "weighted"), (18_000, 60_000, "plain"),
+    (18_001, 20_000, "plain"), (5000, 0, "star"), (16_500, 0, "star")])
+def test_small_graph_chains(ged, n, m, kind):
+    """Graphs whose chains run in one workgroup each (at most 18,000 vertices
+    and 128 K arcs; a single group at most 40 K), around the edges of their
+    slices (64 chunks), register and streaming variants (2^15 arcs) and limits:
+    single scores and batches against the oracle and against the tile path,
+    with rows longer than a chunk, empty and repeated members, S = V."""
+    if kind == "star":  # one row of n - 1 arcs, and a ring for odd cycles
+        leaf = np.arange(1, n, dtype=np.int32)
+        src = np.concatenate([np.zeros(n - 1, np.int32), leaf[:-1]])
+        g = inputs.from_edges(n, src, np.concatenate([leaf, leaf[1:]]))
+    elif m == 0:
+        g = inputs.Graph(n=n, row_ptr=np.zeros(n + 1, np.int64), col_idx=np.zeros(0, np.int32))
+    else:
+        g = _random_graph(n, m, 77 + n, kind == "directed")
+    w = None
+    if kind == "weighted":
+        deg = g.degrees.astype(np.float64)
+        rows = np.repeat(np.arange(g.n), g.degrees)
+        w = 1.0 / np.sqrt(deg[rows] * deg[g.col_idx])
+    gg = ged.GedGraph.from_graph(g, weights=w)
+    alpha = oracle.default_alpha(g, w)
+    say(f"[small graph] {kind} n={g.n} nnz={g.nnz}")
+    groups = [inputs.group(n, min(n, 1), 1), inputs.group(n, min(n, 64), 2),
+              inputs.group(n, min(n, 65), 3), np.arange(n, dtype=np.int32)]
+    groups.append(np.concatenate([groups[1], groups[1][:1]]))  # a repeated member
+    groups.append(np.zeros(0, np.int32))
+    off = np.concatenate([[0], np.cumsum([len(S) for S in groups])]).astype(np.int64)
+    mem = np.concatenate(groups).astype(np.int32)
+    for eps in (1e-2, 1e-5):
+        want = [oracle.score(g, S, alpha, eps, w=w)[0] for S in groups]
+        solo = [gg.score(S, alpha, eps) for S in groups]
+        gg.set_batch_tile(0)
+        batch = gg.score_batch(off, mem, alpha, eps)
+        gg.set_batch_tile(8)
+        tiles = gg.score_batch(off, mem, alpha, eps)
+        for j, c in enumerate(want):
+            assert rel(solo[j], c) <= REL and rel(batch[j], c) <= REL, (eps, j)
+            assert rel(batch[j], tiles[j]) <= 1e-12 and rel(batch[j], solo[j]) <= 1e-12, (eps, j)
+        assert batch[4] == batch[1] and batch[5] == 0.0
+    gg.close()
