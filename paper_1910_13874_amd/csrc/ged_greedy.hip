@@ -585,6 +585,8 @@ struct GreedyCtx {
   int fixed;  // every batch this wide, or 0: batches of a round widen 2, 4, 8, 16
   int Lcap = 0;
   bool split = false;  // undirected: chains to ceil(ell/2) (walk split)
+  bool small = false;  // chains in one workgroup each (ged_small.hip)
+  int join = -1;       // small: vertex that joined S, not in smask yet
   DBuf smask, m_levels, b_levels, ub, stale, done, cand_col, sampled;
   DBuf sdeg;            // split, unweighted: int32 [n] arcs from S into each vertex
   DBuf mc32;            // 2 x uint32 [n]: miss counts of the last two levels (32-bit chain)
@@ -845,6 +847,14 @@ static void compute_bounds(GreedyCtx &c, int ell) {
 // After a pick whose candidate carried a speculative miss column, the levels
 // are copied from it instead of recomputed.
 static void chains_for(GreedyCtx &c, int ell) {
+  if (c.small) {
+    const int a = c.split ? (ell + 1) / 2 : ell;
+    if (c.split) c.Mr.ensure(sizeof(double) * c.n);
+    small_miss(c.g, a, ell - a, c.smask.as<uint32_t>(), c.join, c.m_levels.as<double>(),
+               c.b_levels.as<double>(), c.Mr.as<double>(), c.st);
+    c.join = -1;
+    return;
+  }
   if (!c.split) {
     miss_chains(c, ell);
     return;
@@ -866,19 +876,16 @@ static void chains_for(GreedyCtx &c, int ell) {
   GED_HIP(hipGetLastError());
 }
 
-// Top-K eligible (bound, caller id) pairs, best first, into host arrays.
-static int select_topk(GreedyCtx &c, int K, int round, const int *sampled, int pick, double *hk,
-                       int *hi) {
-  // the launch that leaves one block writes its K pairs straight into the
-  // coherent host buffer
-  double *sk = c.h_small.as<double>();
-  int *si = reinterpret_cast<int *>(sk + 64);
+// Top-K eligible (bound, caller id) pairs, best first: the launches.  The one
+// that leaves one block writes its K pairs to out_k / out_i.
+static void launch_topk(GreedyCtx &c, int K, int round, const int *sampled, int pick,
+                        double *out_k, int *out_i) {
   int nb = topk_blocks(c.n);
   hipLaunchKernelGGL(c.n > kTopSmall ? k_topk_ub<kTopE> : k_topk_ub<kTopESmall>, dim3(nb),
                      dim3(kBlock), 0, c.st, c.ub.as<const double>(), c.done.as<const int>(),
                      round, sampled, pick, c.g->d_old_id.as<const int>(), c.n, K,
-                     nb == 1 ? sk : c.topk_k[0].as<double>(),
-                     nb == 1 ? si : c.topk_i[0].as<int>());
+                     nb == 1 ? out_k : c.topk_k[0].as<double>(),
+                     nb == 1 ? out_i : c.topk_i[0].as<int>());
   GED_HIP(hipGetLastError());
   int cur = 0, count = nb * K;
   while (nb > 1) {
@@ -888,13 +895,19 @@ static int select_topk(GreedyCtx &c, int K, int round, const int *sampled, int p
     hipLaunchKernelGGL(e == kTopE ? k_topk_pairs<kTopE> : k_topk_pairs<kTopESmall>, dim3(nb),
                        dim3(kBlock), 0, c.st, c.topk_k[cur].as<const double>(),
                        c.topk_i[cur].as<const int>(), count, K,
-                       nb == 1 ? sk : c.topk_k[cur ^ 1].as<double>(),
-                       nb == 1 ? si : c.topk_i[cur ^ 1].as<int>());
+                       nb == 1 ? out_k : c.topk_k[cur ^ 1].as<double>(),
+                       nb == 1 ? out_i : c.topk_i[cur ^ 1].as<int>());
     GED_HIP(hipGetLastError());
     cur ^= 1;
     count = nb * K;
   }
-  GED_HIP(hipStreamSynchronize(c.st));
+}
+
+// The pairs a selection left in the coherent host buffer (after the stream
+// has been waited for); returns how many there are.
+static int read_topk(GreedyCtx &c, int K, double *hk, int *hi) {
+  const double *sk = c.h_small.as<double>();
+  const int *si = reinterpret_cast<const int *>(sk + 64);
   int m = 0;
   for (int q = 0; q < K; ++q) {
     if (si[q] == INT_MAX || !(sk[q] >= 0.0)) break;
@@ -902,6 +915,47 @@ static int select_topk(GreedyCtx &c, int K, int round, const int *sampled, int p
     hi[m] = si[q];
     ++m;
   }
+  return m;
+}
+
+static int select_topk(GreedyCtx &c, int K, int round, const int *sampled, int pick, double *hk,
+                       int *hi) {
+  double *sk = c.h_small.as<double>();
+  launch_topk(c, K, round, sampled, pick, sk, reinterpret_cast<int *>(sk + 64));
+  GED_HIP(hipStreamSynchronize(c.st));
+  return read_topk(c, K, hk, hi);
+}
+
+// Small graphs: select Cb + 1 pairs and evaluate the first Cb of them with no
+// host round trip in between; returns the number of pairs.
+static int small_select_eval(GreedyCtx &c, int Cb, int ell, int round, const int *sampled,
+                             int pick, double *hk, int *hi, double *gains) {
+  const int K = Cb + 1;
+  double *sk = c.h_small.as<double>();
+  double *dk = c.gains.as<double>();
+  int *di = c.cand_dev.as<int>();
+  launch_topk(c, K, round, sampled, pick, dk, di);
+  SmallGains b;
+  b.ell = ell;
+  b.width = Cb;
+  b.n_sel = K;
+  b.round = round;
+  b.M = c.m_levels.as<const double>();
+  b.Mr = c.Mr.as<const double>();
+  b.sel_key = dk;
+  b.sel_id = di;
+  b.sel_key_host = sk;
+  b.sel_id_host = reinterpret_cast<int *>(sk + 64);
+  b.smask = c.smask.as<const uint32_t>();
+  b.stale = c.stale.as<double>();
+  b.ub = c.ub.as<double>();
+  b.done = c.done.as<int>();
+  b.gains_host = sk + 256;
+  small_gains(c.g, b, c.st);
+  GED_HIP(hipStreamSynchronize(c.st));
+  const int m = read_topk(c, K, hk, hi);
+  for (int q = 0; q < std::min(m, Cb); ++q) gains[q] = sk[256 + q];
+  c.evals += std::min(m, Cb);
   return m;
 }
 
@@ -1277,6 +1331,8 @@ int greedy_run(ged_graph *g, int32_t k, double alpha, double eps, double eta, ui
   c.fixed = g->greedy_width;
   c.C = c.fixed ? c.fixed : kWidthMax;
   c.split = split_ok(g);
+  c.small = !g->prof.on && small_score_ok(g);
+  c.join = -1;
   c.evals = 0;
   c.rounds = 0;
   c.last_ell = -1;  // nothing of an earlier call is reused
@@ -1290,7 +1346,7 @@ int greedy_run(ged_graph *g, int32_t k, double alpha, double eps, double eta, ui
   c.stale.ensure(sizeof(double) * n);
   c.done.ensure(sizeof(int) * n);
   c.cand_col.ensure(sizeof(int) * n);
-  if (!c.split) {  // ping-pong gain levels (split gains store theirs in dlv)
+  if (!c.split && !c.small) {  // ping-pong gain levels (split gains store theirs in dlv)
     c.X.ensure(sizeof(double) * (size_t)n * c.C);
     c.Y.ensure(sizeof(double) * (size_t)n * c.C);
   }
@@ -1303,7 +1359,7 @@ int greedy_run(ged_graph *g, int32_t k, double alpha, double eps, double eta, ui
   c.topk_i[1].ensure(sizeof(int) * (size_t)nb0 * K);
   c.h_small.ensure(4096, hipHostMallocCoherent);
   launch_fill_i32(c.smask.as<int>(), 0, c.smask.bytes / sizeof(int), c.st);
-  const bool track_sdeg = c.split && !g->weighted;
+  const bool track_sdeg = c.split && !g->weighted && !c.small;
   if (track_sdeg) {
     c.sdeg.ensure(sizeof(int) * (size_t)n);
     launch_fill_i32(c.sdeg.as<int>(), 0, (size_t)n, c.st);
@@ -1403,14 +1459,24 @@ int greedy_run(ged_graph *g, int32_t k, double alpha, double eps, double eta, ui
       int batch_in_round = 0;
       for (;;) {
         const int Cb = batch_width(c, batch_in_round++);
-        const int m = select_topk(c, Cb + 1, round,
-                                  stochastic ? c.sampled.as<const int>() : nullptr, s_size,
-                                  hk.data(), hi.data());
-        if (m == 0) break;
-        if (top.v >= 0 && hk[0] < top.L2) break;  // no bound reaches the runner-up
+        const int *sampled = stochastic ? c.sampled.as<const int>() : nullptr;
+        int m;
+        if (c.small) {
+          // a later batch of a round is reached only when the best bound left
+          // (the last pair selected before) reaches the runner-up
+          m = small_select_eval(c, Cb, ell, round, sampled, s_size, hk.data(), hi.data(),
+                                gains.data());
+          if (m == 0) break;
+        } else {
+          m = select_topk(c, Cb + 1, round, sampled, s_size, hk.data(), hi.data());
+          if (m == 0) break;
+          if (top.v >= 0 && hk[0] < top.L2) break;  // no bound reaches the runner-up
+        }
         const int nc = std::min(m, Cb);
-        for (int q = 0; q < nc; ++q) internal[q] = g->new_id[hi[q]];
-        eval_batch(c, internal.data(), nc, Cb, ell, round, gains.data(), batch_in_round == 1);
+        if (!c.small) {
+          for (int q = 0; q < nc; ++q) internal[q] = g->new_id[hi[q]];
+          eval_batch(c, internal.data(), nc, Cb, ell, round, gains.data(), batch_in_round == 1);
+        }
         for (int q = 0; q < nc; ++q) top.add(gains[q], hi[q]);
         if (m <= Cb) break;  // nothing else eligible
         // the (Cb+1)-th bound is the best among the candidates not evaluated
@@ -1432,7 +1498,10 @@ int greedy_run(ged_graph *g, int32_t k, double alpha, double eps, double eta, ui
         if (tr->evals) tr->evals[s_size] = c.evals;
       }
       s_size++;
-      join(u);
+      if (c.small)
+        c.join = u;  // with the next miss chain
+      else
+        join(u);
       need_chain = true;
       c.sub_col = -1;
       c.spec_col = -1;

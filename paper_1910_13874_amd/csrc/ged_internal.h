@@ -806,6 +806,27 @@ constexpr int kSmallInline = 64;
 void small_scores(ged_graph *g, const int64_t *offs, const int *mem, int groups, double *out,
                   hipStream_t st, int n_inline = -1);
 
+// Miss levels 1 .. levels of S (bits smask, plus the vertex join >= 0, whose
+// bit is set in smask) to M (level i at i*n) -- and the reverse graph's to Mb
+// when directed -- and on undirected graphs Mr = sum_{c<=r} m_c.
+void small_miss(ged_graph *g, int levels, int r, uint32_t *smask, int join, double *M, double *Mb,
+                double *Mr, hipStream_t st);
+// Exact gains at walk length ell of the first `width` of a selection's n_sel
+// pairs (sel_key, caller ids sel_id; INT_MAX past the last), to gains_host;
+// the pairs are copied to sel_key_host / sel_id_host (coherent host memory).
+struct SmallGains {
+  int ell = 0, width = 0, n_sel = 0, round = 0;
+  const double *M = nullptr, *Mr = nullptr;
+  const double *sel_key = nullptr;
+  const int *sel_id = nullptr;
+  double *sel_key_host = nullptr;
+  int *sel_id_host = nullptr;
+  const uint32_t *smask = nullptr;
+  double *stale = nullptr, *ub = nullptr, *gains_host = nullptr;
+  int *done = nullptr;
+};
+void small_gains(ged_graph *g, const SmallGains &b, hipStream_t st);
+
 // Run fn, translating HipError into a status code + message.
 template <class F>
 int guarded(F &&fn) {

@@ -55,6 +55,7 @@ struct SmallGraph {
   size_t lds = 0;
   bool ok = false, tiny = false;
   DBuf buf[2][7];
+  DBuf new_id;  // int [n]: internal id of a caller id
   SmallSide side[2];
 };
 
@@ -73,11 +74,31 @@ struct SmallArgs {
   // of offs and mem
   int cand[kSmallInline];
   int n_inline = -1;
+  // gain: candidate c is the c-th pair (bound, caller id) of a selection of
+  // n_sel; the first workgroup copies the pairs to sel_key_host / sel_id_host
+  const double *sel_key = nullptr;
+  const int *sel_id = nullptr, *new_id = nullptr;
+  int n_sel = 0;
+  double *sel_key_host = nullptr;
+  int *sel_id_host = nullptr;
   // gain: S, and what a round keeps of an evaluated candidate
   const uint32_t *smask = nullptr;
   double *stale = nullptr, *ub = nullptr, *host = nullptr;
   int *done = nullptr;
   int round = 0;
+};
+
+// Miss chains of S (+ join): levels 1 .. levels to M (level i at i*n) and on
+// undirected graphs Mr = sum_{c<=r} m_c; workgroup 1 the reverse graph's.
+struct SmallMissArgs {
+  SmallSide s[2];
+  double *M[2] = {nullptr, nullptr};
+  double *Mr = nullptr;
+  int r = 0;
+  double alpha = 0;
+  int levels = 0;
+  uint32_t *smask = nullptr;
+  int join = -1;  // a vertex whose bit is not in smask yet
 };
 
 // Column totals: every level summed (directed graphs); the walk split at even
@@ -238,7 +259,16 @@ __global__ __launch_bounds__(kSmallThreads) void k_small_chain(SmallArgs a) {
   cols.load(s);
   small_rows<P>(s, l, row, slot, q);
   const int words = (n + 31) / 32;
-  const int x0 = GAIN ? a.cand[blockIdx.x] : -1;
+  int x0 = -1;
+  if constexpr (GAIN) {
+    if (blockIdx.x == 0 && t < a.n_sel) {
+      a.sel_key_host[t] = a.sel_key[t];
+      a.sel_id_host[t] = a.sel_id[t];
+    }
+    const int id = a.sel_id[blockIdx.x];
+    if (id < 0 || id >= n) return;  // fewer candidates than workgroups (all threads)
+    x0 = a.new_id[id];
+  }
   for (int v = t; v <= n; v += kSmallThreads) l.x[v] = v == x0 ? 1.0 : 0.0;
   for (int w = t; w < words; w += kSmallThreads) l.bits[w] = GAIN ? a.smask[w] : 0u;
   __syncthreads();
@@ -309,6 +339,40 @@ __global__ __launch_bounds__(kSmallThreads) void k_small_chain(SmallArgs a) {
   }
 }
 
+template <int P, int J, bool WGT>
+__global__ __launch_bounds__(kSmallThreads) void k_small_miss(SmallMissArgs a) {
+  const bool rev = blockIdx.x == 1;
+  const SmallSide &s = rev ? a.s[1] : a.s[0];
+  double *M = rev ? a.M[1] : a.M[0];
+  const SmallLds l = small_lds(s);
+  const int t = threadIdx.x, n = s.n;
+  int row[P], slot[P];
+  double q[P];
+  SmallCols<P, J> cols;
+  cols.load(s);
+  small_rows<P>(s, l, row, slot, q);
+  for (int w = t; w < (n + 31) / 32; w += kSmallThreads) {
+    uint32_t b = a.smask[w];
+    if (a.join >= 0 && (a.join >> 5) == w) {
+      b |= 1u << (a.join & 31);
+      if (!rev) a.smask[w] = b;  // both workgroups may read either value: same bits
+    }
+    l.bits[w] = b;
+  }
+  __syncthreads();
+  auto bit = [&](int v) { return (l.bits[v >> 5] >> (v & 31)) & 1u; };
+  for (int v = t; v <= n; v += kSmallThreads) l.x[v] = v < n && !bit(v) ? 1.0 : 0.0;
+  __syncthreads();
+  for (int i = 1; i <= a.levels; ++i)
+    small_level<P, J, WGT>(s, cols, l, row, slot, q, [&](int v, double sum, double &qv) {
+      const double y = bit(v) ? 0.0 : a.alpha * sum;
+      l.x[v] = y;
+      M[(size_t)i * n + v] = y;
+      if (i <= a.r) qv += y;
+      if (i == a.levels && a.Mr) a.Mr[v] = qv;
+    });
+}
+
 // ------------------------------------------------------------------ host --
 
 static void small_build(ged_graph *g, bool reverse, SmallGraph &sg, int L,
@@ -373,18 +437,25 @@ static void small_build(ged_graph *g, bool reverse, SmallGraph &sg, int L,
                                 sizeof(uint32_t) * (((size_t)n + 31) / 32));
 }
 
+enum SmallKind { kScoreChain, kGainChain, kMissChain };
+
 template <int P, int J, bool WGT>
-static void small_launch(const SmallArgs &a, bool gain, int grid, size_t lds, hipStream_t st) {
-  if (gain)
+static void small_launch(const void *args, SmallKind kind, int grid, size_t lds,
+                         hipStream_t st) {
+  if (kind == kMissChain)
+    hipLaunchKernelGGL((k_small_miss<P, J, WGT>), dim3(grid), dim3(kSmallThreads), lds, st,
+                       *static_cast<const SmallMissArgs *>(args));
+  else if (kind == kGainChain)
     hipLaunchKernelGGL((k_small_chain<P, J, WGT, true>), dim3(grid), dim3(kSmallThreads), lds, st,
-                       a);
+                       *static_cast<const SmallArgs *>(args));
   else
     hipLaunchKernelGGL((k_small_chain<P, J, WGT, false>), dim3(grid), dim3(kSmallThreads), lds, st,
-                       a);
+                       *static_cast<const SmallArgs *>(args));
 }
 
+// args: SmallMissArgs for kMissChain, else SmallArgs.
 template <bool WGT>
-static void small_run(const SmallGraph &sg, const SmallArgs &a, bool gain, int grid,
+static void small_run(const SmallGraph &sg, const void *a, SmallKind gain, int grid,
                       hipStream_t st) {
   const int p = sg.passes;
   // sources in registers: up to four chunks of kSmallTinyChunk arcs per lane
@@ -424,6 +495,9 @@ static SmallGraph &small_graph(ged_graph *g) {
     }
     small_build(g, r == 1, *sg, L, ci, w);
   }
+  sg->new_id.ensure(sizeof(int) * (size_t)g->n);
+  GED_HIP(hipMemcpy(sg->new_id.p, g->new_id.data(), sizeof(int) * (size_t)g->n,
+                    hipMemcpyHostToDevice));
   sg->ok = sg->passes <= kSmallPasses && sg->lds <= kSmallLds;
   g->small = sg;
   return *g->small;
@@ -459,9 +533,61 @@ void small_scores(ged_graph *g, const int64_t *offs, const int *mem, int groups,
   a.offs = offs;
   a.out = out;
   if (g->weighted)
-    small_run<true>(sg, a, false, groups, st);
+    small_run<true>(sg, &a, kScoreChain, groups, st);
   else
-    small_run<false>(sg, a, false, groups, st);
+    small_run<false>(sg, &a, kScoreChain, groups, st);
+}
+
+void small_miss(ged_graph *g, int levels, int r, uint32_t *smask, int join, double *M, double *Mb,
+                double *Mr, hipStream_t st) {
+  const SmallGraph &sg = small_graph(g);
+  SmallMissArgs a;
+  const bool directed = g->flags == GED_DIRECTED;
+  a.s[0] = sg.side[0];
+  a.s[1] = sg.side[directed ? 1 : 0];
+  a.M[0] = M;
+  a.M[1] = Mb;
+  a.Mr = directed ? nullptr : Mr;
+  a.r = r;
+  a.alpha = g->prep.alpha;
+  a.levels = levels;
+  a.smask = smask;
+  a.join = join;
+  if (g->weighted)
+    small_run<true>(sg, &a, kMissChain, directed ? 2 : 1, st);
+  else
+    small_run<false>(sg, &a, kMissChain, directed ? 2 : 1, st);
+}
+
+void small_gains(ged_graph *g, const SmallGains &b, hipStream_t st) {
+  const SmallGraph &sg = small_graph(g);
+  SmallArgs a;
+  a.s = sg.side[0];
+  a.alpha = g->prep.alpha;
+  a.levels = b.ell;
+  a.mode = kSum;
+  if (split_ok(g)) {
+    a.levels = (b.ell + 1) / 2;
+    a.mode = b.ell % 2 == 0 ? kEven : kOdd;
+  }
+  a.inj = b.M;
+  a.tr = b.Mr;
+  a.sel_key = b.sel_key;
+  a.sel_id = b.sel_id;
+  a.new_id = sg.new_id.as<const int>();
+  a.n_sel = b.n_sel;
+  a.sel_key_host = b.sel_key_host;
+  a.sel_id_host = b.sel_id_host;
+  a.smask = b.smask;
+  a.stale = b.stale;
+  a.ub = b.ub;
+  a.done = b.done;
+  a.round = b.round;
+  a.host = b.gains_host;
+  if (g->weighted)
+    small_run<true>(sg, &a, kGainChain, b.width, st);
+  else
+    small_run<false>(sg, &a, kGainChain, b.width, st);
 }
 
 }  // namespace ged
