@@ -657,7 +657,7 @@ int greedy_width_for(const ged_graph *g) {
 }
 
 static size_t step_ws_bytes(const StepWs &w) {
-  return w.blk.bytes + w.seg.bytes + w.lng.bytes + w.red2.bytes;
+  return w.blk.bytes + w.seg.bytes + w.lng.bytes + w.red2.bytes + w.cnt.bytes;
 }
 
 size_t greedy_bytes_held(const ged_graph *g) {
@@ -710,7 +710,7 @@ size_t greedy_footprint(ged_graph *g, int ell_max, int k) {
   // source-bucketed ones)
   size_t parts = 0;
   auto fields = [&parts](const Partition &p, size_t *f) {
-    parts += p.device_bytes();
+    parts += p.device_bytes() + sizeof(unsigned) * (size_t)(p.n_long + 64);  // and its counters
     f[0] = std::max(f[0], 8 * (size_t)std::max(1, p.n_blocks) * p.C);
     f[1] = std::max(f[1], 8 * (size_t)std::max(1, p.n_segs) * p.C);
     f[2] = std::max(f[2], 8 * (size_t)std::max(1, p.n_long) * p.C);

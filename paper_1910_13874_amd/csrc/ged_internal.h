@@ -184,6 +184,13 @@ constexpr int kSegDoubles = 8192;      // nnz*C handled by one long-row segment
 // (4 FP64 columns): the step takes 924 instead of 1009 us; single-column
 // steps were slower, so by default only gathers of 2 to 4 units are bucketed.
 constexpr int kMaxCutDiv = 4;
+// Most segments of a partition whose last ones finish the long rows inside the
+// step (seg_finish) instead of a fix-up launch: the launch costs 3 to 5 us
+// whatever it does, the counting a round trip per segment.  Directed R-MAT
+// scale 17 (970 K arcs) score 119 -> 106 us and greedy 4.34 -> 3.87 ms without
+// the launch; R-MAT scale 22 score 1,145 -> 1,171 us, scale 20 batches of 32
+// columns 16.3 -> 17.9 ms, so those keep it.
+constexpr int kInlineFixSegs = 2048;
 constexpr int kXcds = 8;                       // XCDs of the device (dispatch round-robin)
 constexpr int64_t kBucketBytes = 3 << 20;      // gathered bytes per source bucket
 constexpr int64_t kBucketAutoBytes = 24 << 20; // bucket long rows above this gathered size
@@ -341,6 +348,10 @@ struct StepArgs {
   // source-bucketed partitions (set by the launch from the partition)
   const int *bk_ci = nullptr;   // sources of the pieces
   const int *bk_ptr = nullptr;  // [pieces+1] first arc of each piece
+  // segments: finished ones per long row, all zero between steps (null: a
+  // fix-up launch follows), and the partition's long rows
+  unsigned *seg_cnt = nullptr;
+  const int *long_rows = nullptr, *long_first = nullptr;
 };
 
 // Walk-count step: Y = epilogue(alpha * A X) with column sums.  Three
@@ -404,21 +415,29 @@ __host__ __device__ constexpr int gather_units(int C, int in_mode, bool weighted
                                                                                            : C;
 }
 
+void launch_fill_i32(int *p, int v, size_t count, hipStream_t st);
+
 // Partial-sum buffers of one step stream (each path owns its own, so captured
 // graphs never see a buffer another path reallocated).
 struct StepWs {
-  DBuf blk, seg, lng, red2;
+  DBuf blk, seg, lng, red2, cnt;
   void fit(const Partition &p) {
     blk.ensure(sizeof(double) * (size_t)(p.n_blocks > 0 ? p.n_blocks : 1) * p.C);
     seg.ensure(sizeof(double) * (size_t)(p.n_segs > 0 ? p.n_segs : 1) * p.C);
     lng.ensure(sizeof(double) * (size_t)(p.n_long > 0 ? p.n_long : 1) * p.C);
     red2.ensure(sizeof(double) * (size_t)kReduceBlocks * p.C);
+    if (p.n_long > 0 && cnt.bytes < sizeof(unsigned) * (size_t)p.n_long) {
+      cnt.ensure(sizeof(unsigned) * (size_t)p.n_long);
+      launch_fill_i32(cnt.as<int>(), 0, cnt.bytes / sizeof(int), nullptr);
+      GED_HIP(hipStreamSynchronize(nullptr));
+    }
   }
   double *scratch() const { return red2.as<double>(); }
   void into(StepArgs &a) const {
     a.blk_part = blk.as<double>();
     a.seg_out = seg.as<double>();
     a.long_part = lng.as<double>();
+    a.seg_cnt = cnt.as<unsigned>();
   }
 };
 

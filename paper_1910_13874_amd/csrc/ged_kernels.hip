@@ -23,8 +23,9 @@
 //     CU: the random gathers are latency-bound, and more resident blocks
 //     keep more of them in flight.
 //   * long rows (more arcs than a row block holds, the power-law hubs): split
-//     into fixed segments, one block each, whose raw sums go to seg_out; a
-//     fix-up kernel adds the segments of each row in order.
+//     into fixed segments, one block each, whose raw sums go to seg_out; the
+//     last of a row's segments to finish adds them in order (seg_finish), or,
+//     where there are many, a fix-up kernel does.
 //   * a reduction kernel sums the block and long-row partials of each column
 //     in a fixed order.
 // Combining epilogues (split scoring and split gains, undirected graphs) do not
@@ -628,6 +629,88 @@ constexpr int step_waves() {
   return !WGT && IN == IN_CNT16 && OUT == OUT_COMBINE16 ? 8 : 1;
 }
 
+// Long row l (row r), column c, given the sum of its segments or pieces:
+// apply the epilogue and keep the output for the column sums.
+template <int C, int OUT>
+__device__ __forceinline__ void fixup_tail(const StepArgs &a, int l, int r, int c, double acc) {
+  double y = epilogue<C, OUT>(a, r, c, acc);
+  if constexpr (OUT == OUT_GAINCOMB) {
+    if (c >= a.spec_from) {  // miss column: its level is stored, not combined
+      a.Y[(size_t)r * C + c] = y;
+      a.long_part[(size_t)l * C + c] = 0.0;
+      return;
+    }
+  }
+  if constexpr (OutTraits<OUT>::cstore)
+    a.Y32[(size_t)r * C + c] = gain_count(a, y, acc, a.cand_col[r] == c);
+  if constexpr (OutTraits<OUT>::combine) {
+    CombineFor<C, OUT> in;
+    in.load(a, r, c);
+    const bool member = OutTraits<OUT>::gaincomb ? false : ((a.tmask[r] >> c) & 1ull);
+    double top;
+    const double q = in.q(a, r, c, top);
+    if (!OutTraits<OUT>::gaincomb && a.q_quad)
+      y = combine_quad(q, top, a.alpha * acc, in.trv, in.ta, member);
+    else
+      y = combine_fin(a, q, y, in.trv, in.ta, member);
+  } else if constexpr (OUT == OUT_ZERO32 || OUT == OUT_GAIN32D) {
+    a.Y32[(size_t)r * C + c] = (uint32_t)y;
+    a.Y[(size_t)r * C + c] = a.alpha * y;
+  } else if constexpr (OutTraits<OUT>::store32) {
+    if (OUT != OUT_TILE32H || !a.y32_marked || y > (double)kC16Max)
+      a.Y32[(size_t)r * C + c] = (uint32_t)y;
+    if constexpr (OUT == OUT_TILE32H)
+      a.Y16[(size_t)r * C + c] = (uint16_t)(y > (double)kC16Max ? kC16Hub : (uint32_t)y);
+  } else {
+    a.Y[(size_t)r * C + c] = y;
+  }
+  double *lp = a.long_part + (size_t)l * C + c;
+  *lp = a.accum ? *lp + y : y;
+}
+
+// A segment of long row l has written its C column sums to out (threads
+// t < C, all in the first wavefront): the row's last segment to do so -- the
+// only one of most long rows -- adds them in a fixed order and finishes the
+// row.  As a launch of its own this took 3 to 5 us per step, a third of a
+// small graph's step.  The sums are exchanged by agent-scope atomic stores
+// and loads, which are coherent between the XCDs by themselves, ordered by
+// waiting for the stores before the count: a device fence would write back
+// the XCD's whole L2 per segment (R-MAT scale 22, one column: 540 -> 915 us).
+template <int C, int OUT>
+__device__ __forceinline__ void seg_finish(const StepArgs &a, int l, double *out) {
+  const int t = threadIdx.x;
+  if (a.seg_cnt == nullptr || t >= 64) return;
+  const int q0 = a.long_first[l], q1 = a.long_first[l + 1];
+  if (q1 - q0 == 1) {
+    if (t < C) fixup_tail<C, OUT>(a, l, a.long_rows[l], t, out[t]);
+    return;
+  }
+  if (t < C) __hip_atomic_store(&out[t], out[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the sums before the count
+  unsigned old = 0;
+  if (t == 0)
+    old = __hip_atomic_fetch_add(&a.seg_cnt[l], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if ((int)__builtin_amdgcn_readfirstlane(old) != q1 - q0 - 1) return;
+  asm volatile("" ::: "memory");
+  if (t == 0) a.seg_cnt[l] = 0;  // for the next step
+  constexpr int S = 64 / C;      // lanes per column
+  const int c = t & (C - 1);
+  double s4[4] = {0.0, 0.0, 0.0, 0.0};  // four loads in flight
+  auto seg = [&](int q) {
+    return __hip_atomic_load(&a.seg_out[(size_t)q * C + c], __ATOMIC_RELAXED,
+                             __HIP_MEMORY_SCOPE_AGENT);
+  };
+  int q = q0 + t / C;
+  for (; q + 3 * S < q1; q += 4 * S) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) s4[k] += seg(q + k * S);
+  }
+  for (; q < q1; q += S) s4[0] += seg(q);
+  double acc = (s4[0] + s4[1]) + (s4[2] + s4[3]);
+  for (int o = C; o < 64; o <<= 1) acc += __shfl_xor(acc, o, 64);
+  if (t < C) fixup_tail<C, OUT>(a, l, a.long_rows[l], c, acc);
+}
+
 template <int C, int IN, int OUT, bool WGT>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(step_waves<C, IN, OUT, WGT>())))
 void k_step(StepArgs a, const int4 *__restrict__ blocks,
@@ -967,6 +1050,7 @@ void k_step(StepArgs a, const int4 *__restrict__ blocks,
       }
     }
     block_colsum_quads<C>(acc, red, a.seg_out + (size_t)(b - n_blocks) * C);
+    seg_finish<C, OUT>(a, sd.w, a.seg_out + (size_t)(b - n_blocks) * C);
   } else if constexpr (NP) {
     // One segment of a long row, column pairs: kBlock / CU lanes per pair.
     const int4 sd = segs[b - n_blocks];
@@ -991,6 +1075,7 @@ void k_step(StepArgs a, const int4 *__restrict__ blocks,
       }
     }
     block_colsum_pairs<C>(acc0, acc1, red, a.seg_out + (size_t)(b - n_blocks) * C);
+    seg_finish<C, OUT>(a, sd.w, a.seg_out + (size_t)(b - n_blocks) * C);
   } else {
     // One segment of a long row: LPC lanes per column stride over its arcs.
     const int4 sd = segs[b - n_blocks];
@@ -1012,50 +1097,13 @@ void k_step(StepArgs a, const int4 *__restrict__ blocks,
       for (int q = 0; q < U; ++q) acc += (j0 + q * LPC < sd.z) ? v[q] : 0.0;
     }
     block_colsum<C>(acc, 1, red, a.seg_out + (size_t)(b - n_blocks) * C, 0);
+    if constexpr (!HC) seg_finish<C, OUT>(a, sd.w, a.seg_out + (size_t)(b - n_blocks) * C);
   }
 }
 
-// Long row l (row r), column c, given the sum of its segments or pieces:
-// apply the epilogue and keep the output for the column sums.
-template <int C, int OUT>
-__device__ __forceinline__ void fixup_tail(const StepArgs &a, int l, int r, int c, double acc) {
-  double y = epilogue<C, OUT>(a, r, c, acc);
-  if constexpr (OUT == OUT_GAINCOMB) {
-    if (c >= a.spec_from) {  // miss column: its level is stored, not combined
-      a.Y[(size_t)r * C + c] = y;
-      a.long_part[(size_t)l * C + c] = 0.0;
-      return;
-    }
-  }
-  if constexpr (OutTraits<OUT>::cstore)
-    a.Y32[(size_t)r * C + c] = gain_count(a, y, acc, a.cand_col[r] == c);
-  if constexpr (OutTraits<OUT>::combine) {
-    CombineFor<C, OUT> in;
-    in.load(a, r, c);
-    const bool member = OutTraits<OUT>::gaincomb ? false : ((a.tmask[r] >> c) & 1ull);
-    double top;
-    const double q = in.q(a, r, c, top);
-    if (!OutTraits<OUT>::gaincomb && a.q_quad)
-      y = combine_quad(q, top, a.alpha * acc, in.trv, in.ta, member);
-    else
-      y = combine_fin(a, q, y, in.trv, in.ta, member);
-  } else if constexpr (OUT == OUT_ZERO32 || OUT == OUT_GAIN32D) {
-    a.Y32[(size_t)r * C + c] = (uint32_t)y;
-    a.Y[(size_t)r * C + c] = a.alpha * y;
-  } else if constexpr (OutTraits<OUT>::store32) {
-    if (OUT != OUT_TILE32H || !a.y32_marked || y > (double)kC16Max)
-      a.Y32[(size_t)r * C + c] = (uint32_t)y;
-    if constexpr (OUT == OUT_TILE32H)
-      a.Y16[(size_t)r * C + c] = (uint16_t)(y > (double)kC16Max ? kC16Hub : (uint32_t)y);
-  } else {
-    a.Y[(size_t)r * C + c] = y;
-  }
-  double *lp = a.long_part + (size_t)l * C + c;
-  *lp = a.accum ? *lp + y : y;
-}
-
-// Long rows cut into segments: one thread per (row, column) adds the row's
-// segment sums in segment order.
+// Long rows cut into segments, where there are many (kInlineFixSegs) or the
+// caller has no counters for seg_finish (ged_score_noalloc): one thread per
+// (row, column) adds the row's segment sums in segment order.
 template <int C, int OUT>
 __global__ __launch_bounds__(kBlock) void k_fixup(StepArgs a, const int *__restrict__ long_rows,
                                                   const int *__restrict__ long_first, int n_long) {
@@ -1167,6 +1215,11 @@ static void launch_t(const Partition &p, const StepArgs &a, hipStream_t st, hipE
   if (bk && C > 8) throw HipError{GED_ERR_ARG, "source buckets at more than 8 columns"};
   b.bk_ci = bk ? p.bk_ci.as<const int>() : nullptr;
   b.bk_ptr = bk ? p.bk_ptr.as<const int>() : nullptr;
+  b.long_rows = p.long_rows.as<const int>();
+  b.long_first = p.long_first.as<const int>();
+  // single-column count steps keep the launch at any size: the extra code
+  // alone slowed R-MAT scale 22's by 3 %
+  if (p.n_segs > kInlineFixSegs || (C == 1 && IN == IN_CNT32 && !WGT)) b.seg_cnt = nullptr;
   if (grid > 0)
     hipLaunchKernelGGL((k_step<C, IN, OUT, WGT>), dim3(grid), dim3(kBlock), 0, st, b,
                        p.blocks.as<const int4>(), p.segs.as<const int4>(), p.n_blocks);
@@ -1177,7 +1230,7 @@ static void launch_t(const Partition &p, const StepArgs &a, hipStream_t st, hipE
                        dim3((p.n_long + rows_per_block - 1) / rows_per_block), dim3(kBlock), 0, st,
                        b, p.long_rows.as<const int>(), p.long_first.as<const int>(),
                        p.bk_lsub.as<const int>(), p.n_long);
-  } else if (p.n_long > 0) {
+  } else if (p.n_long > 0 && !b.seg_cnt) {
     const int thr = p.n_long * C;
     hipLaunchKernelGGL((k_fixup<C, OUT>), dim3((thr + kBlock - 1) / kBlock), dim3(kBlock), 0, st,
                        b, p.long_rows.as<const int>(), p.long_first.as<const int>(), p.n_long);

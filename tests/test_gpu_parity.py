@@ -1453,3 +1453,42 @@ def test_small_graph_chains(ged, n, m, kind):
             assert rel(batch[j], tiles[j]) <= 1e-12 and rel(batch[j], solo[j]) <= 1e-12, (eps, j)
         assert batch[4] == batch[1] and batch[5] == 0.0
     gg.close()
+
+
+@pytest.mark.parametrize("kind", ["directed", "weighted"])
+def test_long_rows_finished_in_the_step(ged, kind):
+    """Long rows whose last segment finishes them inside the step: rows of one
+    segment, of two and of many beside each other (2,100, 9,000 and 60,000 arcs
+    at one column, more segments at wider tiles), repeated calls (the counters
+    return to zero), scores, batches and the greedy against the oracle."""
+    n = 70_000
+    r = inputs.uniform_ints(2 * 30_000, n, 5).astype(np.int32)
+    hubs = [(0, 2100), (1, 9000), (2, 60_000), (3, 700)]
+    src = np.concatenate([r[0::2]] + [np.arange(10, 10 + d, dtype=np.int32) for _, d in hubs])
+    dst = np.concatenate([r[1::2]] + [np.full(d, h, np.int32) for h, d in hubs])
+    g = inputs.from_edges(n, src, dst, symmetrize=kind != "directed")
+    w = None
+    if kind == "weighted":
+        deg = g.degrees.astype(np.float64)
+        rows = np.repeat(np.arange(g.n), g.degrees)
+        w = 1.0 / np.sqrt(deg[rows] * deg[g.col_idx])
+    gg = ged.GedGraph.from_graph(g, weights=w)
+    alpha = 0.5 * oracle.default_alpha(g, w)
+    say(f"[long rows] {kind} n={g.n} nnz={g.nnz}")
+    groups = [inputs.group(n, 5, 1), np.array([2], np.int32), np.array([0, 1, 3], np.int32),
+              inputs.group(n, 300, 2)]
+    off = np.concatenate([[0], np.cumsum([len(S) for S in groups])]).astype(np.int64)
+    mem = np.concatenate(groups).astype(np.int32)
+    want = [oracle.score(g, S, alpha, EPS, w=w)[0] for S in groups]
+    for _ in range(2):
+        for S, c in zip(groups, want):
+            assert rel(gg.score(S, alpha, EPS), c) <= REL
+        for tile in (1, 4, 16):
+            gg.set_batch_tile(tile)
+            s = gg.score_batch(off, mem, alpha, EPS)
+            assert max(rel(x, c) for x, c in zip(s, want)) <= REL, tile
+    o = oracle.greedy(g, 3, alpha, 1e-2, w=w)
+    for width in (0, 2, 16):
+        gg.set_greedy_width(width)
+        compare_greedy(gg.greedy(3, alpha, 1e-2), o, (kind, width))
+    gg.close()
