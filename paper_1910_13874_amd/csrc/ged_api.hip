@@ -628,6 +628,13 @@ static int create_impl(int64_t n, int64_t nnz, const int64_t *row_ptr, const int
     if (flags == GED_UNDIRECTED && !weights && nnz > 0 &&
         (int64_t)hc.irp[(size_t)h] * kHubShareDiv >= nnz)
       g->hc_rows = h;
+    // the same of the lower arcs: the first rows' arcs that are others' lower ones
+    g->h_rp_l = std::move(hc.lrp);
+    if (!g->h_rp_l.empty()) {
+      const int64_t nl = g->h_rp_l[(size_t)n];
+      if (nl > 0 && ((int64_t)hc.irp[(size_t)h] - g->h_rp_l[(size_t)h]) * kHubShareDiv >= nl)
+        g->hc_rows_l = h;
+    }
   }
   const std::vector<int> &irp = hc.irp, &ici = hc.ici, &orp = hc.orp, &oci = hc.oci;
   const std::vector<double> &iw = hc.iw, &ow = hc.ow;

@@ -579,10 +579,10 @@ struct ged_graph {
   std::mutex parts_mu;
   std::map<int, std::unique_ptr<ged::Partition>> parts, parts_r;
   // lower arcs (undirected unweighted graphs): of each row the sources before
-  // it in the internal order, a prefix of the row; built on first use
+  // it in the internal order, a prefix of the row; on the device from the
+  // first use on
   std::mutex lower_mu;
   bool lower_ready = false;
-  int64_t nnz_l = 0;
   std::vector<int> h_rp_l;
   ged::DBuf rp_l, ci_l;
   int hc_rows_l = 0;            // as hc_rows, for the lower arcs

@@ -710,23 +710,6 @@ static Partition &final_partition(ged_graph *g, const SplitPlan &pl, int C) {
                  : step_partition(g, pl, C, in);
 }
 
-// Lower arcs: lower[v] = sources of row v before v (rows are sorted).
-__global__ void k_lower_count(const int *__restrict__ rp, const int *__restrict__ ci, int n,
-                              int *__restrict__ lower) {
-  for (int v = blockIdx.x * blockDim.x + threadIdx.x; v < n; v += gridDim.x * blockDim.x) {
-    int lo = rp[v], hi = rp[v + 1];
-    const int b = lo;
-    while (lo < hi) {
-      const int mid = lo + (hi - lo) / 2;
-      if (ci[mid] < v)
-        lo = mid + 1;
-      else
-        hi = mid;
-    }
-    lower[v] = lo - b;
-  }
-}
-
 // Eight lanes per row copy its lower arcs.
 __global__ __launch_bounds__(kBlock) void k_lower_copy(const int *__restrict__ rp,
                                                        const int *__restrict__ ci,
@@ -744,32 +727,15 @@ void ensure_lower(ged_graph *g, hipStream_t st) {
   std::lock_guard<std::mutex> lk(g->lower_mu);
   if (g->lower_ready) return;
   const int n = (int)g->n;
-  const int *rp = g->rp.as<const int>(), *ci = g->ci.as<const int>();
-  DBuf cnt;
-  cnt.ensure(sizeof(int) * (size_t)n);
-  hipLaunchKernelGGL(k_lower_count, dim3(grid_for(((int64_t)n + kBlock - 1) / kBlock, 8192)),
-                     dim3(kBlock), 0, st, rp, ci, n, cnt.as<int>());
-  GED_HIP(hipGetLastError());
-  std::vector<int> h((size_t)n + 1);
-  GED_HIP(hipMemcpyAsync(h.data() + 1, cnt.p, sizeof(int) * (size_t)n, hipMemcpyDeviceToHost, st));
-  GED_HIP(hipStreamSynchronize(st));
-  h[0] = 0;
-  for (int v = 0; v < n; ++v) h[(size_t)v + 1] += h[(size_t)v];
-  const int64_t nl = h[(size_t)n];
   g->rp_l.ensure(sizeof(int) * (size_t)(n + 1));
-  g->ci_l.ensure(sizeof(int) * (size_t)std::max<int64_t>(1, nl));
-  GED_HIP(hipMemcpyAsync(g->rp_l.p, h.data(), sizeof(int) * (size_t)(n + 1),
+  g->ci_l.ensure(sizeof(int) * (size_t)std::max<int64_t>(1, g->h_rp_l[(size_t)n]));
+  GED_HIP(hipMemcpyAsync(g->rp_l.p, g->h_rp_l.data(), sizeof(int) * (size_t)(n + 1),
                          hipMemcpyHostToDevice, st));
   hipLaunchKernelGGL(k_lower_copy, dim3(grid_for(((int64_t)n + kBlock / 8 - 1) / (kBlock / 8), 65536)),
-                     dim3(kBlock), 0, st, rp, ci, g->rp_l.as<const int>(), n, g->ci_l.as<int>());
+                     dim3(kBlock), 0, st, g->rp.as<const int>(), g->ci.as<const int>(),
+                     g->rp_l.as<const int>(), n, g->ci_l.as<int>());
   GED_HIP(hipGetLastError());
   GED_HIP(hipStreamSynchronize(st));
-  // the first rows' share as sources: their arcs that are lower arcs of others
-  const int hc = std::min(kHubRows, n);
-  const int64_t hub = (int64_t)g->h_rp[(size_t)hc] - h[(size_t)hc];
-  g->hc_rows_l = nl > 0 && hub * kHubShareDiv >= nl ? hc : 0;
-  g->nnz_l = nl;
-  g->h_rp_l.swap(h);
   g->lower_ready = true;
 }
 

@@ -31,6 +31,8 @@ struct HostCsr {
   std::vector<int> new_id, old_id;  // caller id -> internal id, and back
   std::vector<int> irp, ici;        // in-rows: row v lists u for every arc u -> v
   std::vector<double> iw;           // their weights (weighted graphs)
+  std::vector<int> lrp;             // [n+1] row pointers of the lower arcs (u < v, a prefix of
+                                    // each row; undirected unweighted graphs)
   std::vector<int> orp, oci;        // out-rows (the reverse graph; oci and ow
   std::vector<double> ow;           // directed graphs only: undirected ones equal irp/ici)
   int32_t max_deg = 0;              // maximum out-degree
@@ -267,6 +269,7 @@ inline const char *build_host_csr(int64_t n, int64_t nnz, const int64_t *row_ptr
     // undirected graph are the same rows and are not built
     out.ici.assign(ne, 0);
     out.iw.assign(weights ? ne : 0, 0.0);
+    out.lrp.assign(weights ? 0 : (size_t)N + 1, 0);
     std::vector<int64_t> ip(out.irp.begin(), out.irp.end());
     const std::vector<int64_t> b = split_rows(ip.data(), n, T);
     run_threads(T, [&](int t) {
@@ -278,6 +281,7 @@ inline const char *build_host_csr(int64_t n, int64_t nnz, const int64_t *row_ptr
         if (!weights) {
           for (int64_t k = 0; k < len; ++k) dst[k] = nid[col_idx[j0 + k]];
           std::sort(dst, dst + len);
+          out.lrp[(size_t)nv + 1] = (int)(std::lower_bound(dst, dst + len, (int)nv) - dst);
         } else {
           key.resize((size_t)len);
           for (int64_t k = 0; k < len; ++k)
@@ -291,6 +295,7 @@ inline const char *build_host_csr(int64_t n, int64_t nnz, const int64_t *row_ptr
         }
       }
     });
+    for (size_t v = 0; v + 1 < out.lrp.size(); ++v) out.lrp[v + 1] += out.lrp[v];
   } else {
     // ---- out-rows: row nu lists nv for every arc u -> v, the caller's rows
     // taken in internal order
