@@ -166,7 +166,8 @@ static int autotune_tile(ged_graph *g, BatchWs &b) {
 // Split scoring: the same race over the dense levels of a split tile (the
 // level-(s+1) step on count rows and the combining step), at C = 8..64; best
 // of two timed passes after a warm-up.
-static int autotune_split(ged_graph *g, BatchWs &b, const SplitPlan &pl0) {
+static int autotune_split(ged_graph *g, BatchWs &b, const SplitPlan &pl0, double push2_per_group,
+                          int64_t max_group) {
   if (g->batch_tile > 0 && g->batch_cut_div > 0) return g->batch_tile;
   hipStream_t st = g->stream;
   hipEvent_t e0, e1;
@@ -176,6 +177,8 @@ static int autotune_split(ged_graph *g, BatchWs &b, const SplitPlan &pl0) {
     SplitPlan pl = pl0;
     pl.cut_div = cut;
     pl.c16_hub = split_c16_hub(g, pl, C, st);
+    pl.dense2 = split_dense2(g, pl, C, push2_per_group * C);
+    pl.m16 = split_m16(g, pl, C, max_group);
     split_fit(g, b.sw, pl, C, 1, st);
     split_dense(g, b.sw, pl, C, b.tmask.as<const uint64_t>(), st);  // warm-up
     float ms = 1e30f;
@@ -296,7 +299,16 @@ int score_batch(ged_graph *g, const int64_t *offsets, const int32_t *members, in
     pl = split_plan(g, g->prep.ell);
     split_tables(g, pl, st);
   }
-  const int C = split ? autotune_split(g, b, pl) : autotune_tile(g, b);
+  // mean push volume of a group (members' omega_2) and the largest group: what
+  // decides how a tile gets its level 2
+  double push2 = 0.0;
+  int64_t max_group = 0;
+  for (int j = 0; j < G; ++j) max_group = std::max(max_group, offsets[j + 1] - offsets[j]);
+  if (split && pl.s >= 2 && !(g->batch_tile > 0 && g->batch_cut_div > 0)) {
+    const std::vector<double> &om2 = omega2_host(g, st);
+    for (int64_t j = 0; j < M; ++j) push2 += om2[(size_t)g->new_id[members[j]]];
+  }
+  const int C = split ? autotune_split(g, b, pl, push2 / G, max_group) : autotune_tile(g, b);
   pl.cut_div = g->batch_cut_div;
   if (split) pl.c16_hub = split_c16_hub(g, pl, C, st);
   g->c16_used = pl.c16_hub;
@@ -337,6 +349,26 @@ int score_batch(ged_graph *g, const int64_t *offsets, const int32_t *members, in
     GED_HIP(hipMemcpyAsync(b.mcol.p, hcol.data(), sizeof(int) * (size_t)Md,
                            hipMemcpyHostToDevice, st));
   }
+  // per tile: clear its count levels by a fill where replaying its pushes
+  // would cost more (members' omega_2 sum against the levels' size); decided
+  // before any capture (the host table may need a synchronisation once).  A
+  // captured batch keeps the choices of the call that captured it: both
+  // clear everything the pushes wrote, so later groups only differ in speed.
+  // Whether level 2 is gathered is one choice for the whole batch (its mean
+  // tile), kept with the captured graph's key.
+  std::vector<char> fill((size_t)(G + C - 1) / C, 0);
+  if (split && pl.s >= 2 && !pl.push3) {
+    const std::vector<double> &om2 = omega2_host(g, st);
+    double sum = 0.0;
+    for (size_t t = 0; t < fill.size(); ++t) {
+      double v = 0.0;
+      for (int64_t q = hoff[t * C]; q < hoff[std::min(G, (int)(t + 1) * C)]; ++q) v += om2[hmem[q]];
+      fill[t] = split_clear_by_fill(g, pl, C, v) ? 1 : 0;
+      sum += v;
+    }
+    pl.dense2 = split_dense2(g, pl, C, sum / (double)fill.size());
+    pl.m16 = split_m16(g, pl, C, max_group);
+  }
   if (split) {
     size_t wl_need = 1;
     int64_t deg_tile = 1;  // largest member-degree sum of a tile: about its worklist size
@@ -369,25 +401,6 @@ int score_batch(ged_graph *g, const int64_t *offsets, const int32_t *members, in
   } else {
     b.X.ensure(sizeof(double) * (size_t)n * C);
     b.Y.ensure(sizeof(double) * (size_t)n * C);
-  }
-  // per tile: clear its count levels by a fill where replaying its pushes
-  // would cost more (members' omega_2 sum against the levels' size); decided
-  // before any capture (the host table may need a synchronisation once).  A
-  // captured batch keeps the choices of the call that captured it: both
-  // clear everything the pushes wrote, so later groups only differ in speed.
-  // Whether level 2 is gathered is one choice for the whole batch (its mean
-  // tile), kept with the captured graph's key.
-  std::vector<char> fill((size_t)(G + C - 1) / C, 0);
-  if (split && pl.s >= 2 && !pl.push3) {
-    const std::vector<double> &om2 = omega2_host(g, st);
-    double sum = 0.0;
-    for (size_t t = 0; t < fill.size(); ++t) {
-      double v = 0.0;
-      for (int64_t q = hoff[t * C]; q < hoff[std::min(G, (int)(t + 1) * C)]; ++q) v += om2[hmem[q]];
-      fill[t] = split_clear_by_fill(g, pl, C, v) ? 1 : 0;
-      sum += v;
-    }
-    pl.dense2 = split_dense2(g, pl, C, sum / (double)fill.size());
   }
   auto enqueue = [&]() {
     if (!split) {
@@ -445,7 +458,9 @@ int score_batch(ged_graph *g, const int64_t *offsets, const int32_t *members, in
                                    (const void *)(intptr_t)C,
                                    (const void *)(intptr_t)g->batch_cut_div,
                                    (const void *)(intptr_t)pl.c16_hub,
-                                   (const void *)(intptr_t)pl.dense2, g->omega2_f.p, g->ci_l.p};
+                                   (const void *)(intptr_t)pl.dense2, g->omega2_f.p, g->ci_l.p,
+                                   (const void *)(intptr_t)pl.m16, b.sw.cnt1h.p, b.sw.cnt2h.p,
+                                   b.sw2.cnt1h.p, b.sw2.cnt2h.p};
 
   if (g->prof.on) {
     // profiling times every step launch with events: run the batch eagerly

@@ -495,6 +495,10 @@ struct SplitPlan {
   // level 2 gathered from the level-1 counts by a dense step instead of pushed
   // from the group's neighbourhoods (split_dense2)
   bool dense2 = false;
+  // with dense2, tiles of at least 16 columns: levels 1 and 2 also as 16-bit
+  // copies with kC16Hub in place of larger counts, which the level-2 and
+  // level-3 steps gather (split_m16)
+  bool m16 = false;
   int cut_div = 1;  // row-split threshold divisor of the dense steps' partitions
   // level-2 counts in the 16-bit layout with this hub cut (c16_pk_offset),
   // -1: plain 32-bit counts.  Batch tiles of C >= 4 columns only (c32, s = 2,
@@ -506,6 +510,8 @@ struct SplitWs {
   DBuf cnt1, cnt2;       // [n*C] walk counts of levels 1, 2 (uint32 or uint64); zero
                          // between tiles
   DBuf lv;               // [nlv*n*C] stored dense levels (double, or uint32 counts)
+  DBuf cnt1h, cnt2h;     // [n*C] 16-bit copies of levels 1 (zero between tiles) and 2 (m16)
+  bool cnt2_dirty = false;  // left by gathered level 2, to be zeroed before a push
   DBuf lv16;             // [n*C] 16-bit copy of the last stored level (16-bit layout)
   DBuf wl, wl_n;         // uint64 worklist [wl_cap], uint32 length
   unsigned wl_cap = 0;
@@ -795,6 +801,9 @@ bool split_clear_by_fill(const ged_graph *g, const SplitPlan &pl, int C, double 
 // Is level 2 of a tile of C columns cheaper gathered from level 1 by a dense
 // step than pushed?  push2_arcs as above.
 bool split_dense2(const ged_graph *g, const SplitPlan &pl, int C, double push2_arcs);
+// Do the gathers of a gathered level 2 take 16-bit copies (pl.m16)?  max_group:
+// the largest group's size.
+bool split_m16(const ged_graph *g, const SplitPlan &pl, int C, int64_t max_group);
 // All four phases in order on one stream.  profile = false launches without
 // profiling events (the server enqueues tiles from its own thread).
 void enqueue_split_tile(ged_graph *g, SplitWs &w, const SplitPlan &pl, int C,

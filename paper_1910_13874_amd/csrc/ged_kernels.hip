@@ -460,6 +460,7 @@ __device__ __forceinline__ uint32_t half16(uint32_t x, int i) {
 }
 
 // Columns a lane of quad_rows takes.
+typedef double f64x2 __attribute__((ext_vector_type(2)));
 template <int OUT>
 constexpr int quad_cols() {
   return OUT == OUT_COMBINE16 ? 2 : 4;
@@ -512,7 +513,8 @@ struct CombinePair {
   }
 };
 
-// Phase 2 of a 16-bit row block (OUT_TILE32, OUT_TILE32H, OUT_COMBINE16).
+// Phase 2 of a 16-bit row block (OUT_TILE, OUT_TILE32, OUT_TILE32H,
+// OUT_COMBINE16).
 // vals holds the block's arcs, C halves each; of the LA = C/NC lanes per arc,
 // lane t takes columns NC*k .. NC*k + NC - 1, k = t % LA, of row slot
 // t / (LA * tpr), striding the row's arcs by tpr: the lanes of an arc read
@@ -589,6 +591,21 @@ __device__ __forceinline__ void quad_rows(const StepArgs &a, const uint32_t *val
         const double sum = total(i);
         if (s == 0) cs[i] += pf.share(a, r, k, i, sum, (mem >> i) & 1u);
       }
+    } else if constexpr (OUT == OUT_TILE) {  // an FP64 level (its column sums are not used)
+      double y[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) y[i] = a.alpha * total(i);
+      if (s != 0) continue;
+      if (mem) {
+        const double w = a.inj[r];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if ((mem >> i) & 1u) y[i] = w;
+      }
+      double *o = a.Y + (size_t)r * C + NC * k;
+      const f64x2 y0 = {y[0], y[1]}, y1 = {y[2], y[3]};
+      __builtin_nontemporal_store(y0, reinterpret_cast<f64x2 *>(o));
+      __builtin_nontemporal_store(y1, reinterpret_cast<f64x2 *>(o + 2));
     } else {
       // exact counts (alpha = 1); members take the level's omega
       const size_t o = (size_t)r * C + NC * k;
@@ -616,17 +633,6 @@ __device__ __forceinline__ void quad_rows(const StepArgs &a, const uint32_t *val
       }
     }
   }
-}
-
-// Waves per SIMD the register allocation must allow (1: the compiler's
-// choice).  The combining steps over 16-bit counts (57-62 VGPRs) are held to
-// eight, the LDS of eight resident blocks of four waves fitting a CU; at
-// seven they ran 7 % slower.  The bound is not set on the other steps: those
-// within 64 VGPRs already are scheduled differently under it (the FP64 gain
-// step lost 2 %), and the larger ones would spill.
-template <int C, int IN, int OUT, bool WGT>
-constexpr int step_waves() {
-  return !WGT && IN == IN_CNT16 && OUT == OUT_COMBINE16 ? 8 : 1;
 }
 
 // Long row l (row r), column c, given the sum of its segments or pieces:
@@ -709,6 +715,19 @@ __device__ __forceinline__ void seg_finish(const StepArgs &a, int l, double *out
   double acc = (s4[0] + s4[1]) + (s4[2] + s4[3]);
   for (int o = C; o < 64; o <<= 1) acc += __shfl_xor(acc, o, 64);
   if (t < C) fixup_tail<C, OUT>(a, l, a.long_rows[l], c, acc);
+}
+
+// Waves per SIMD the register allocation must allow (1: the compiler's
+// choice).  The combining steps over 16-bit counts are held to eight, the LDS
+// of eight resident blocks of four waves fitting a CU: left alone the compiler
+// takes 62 VGPRs too, but in a schedule 13 % slower (BA n = 2e6, 64 columns:
+// 905 and 1,040 us; the 36 bytes it spills under the bound lie on the path of
+// marked counts and segments).  The bound is not set on the other steps: those
+// within 64 VGPRs already are scheduled differently under it (the FP64 gain
+// step lost 2 %), and the larger ones would spill.
+template <int C, int IN, int OUT, bool WGT>
+constexpr int step_waves() {
+  return !WGT && IN == IN_CNT16 && OUT == OUT_COMBINE16 ? 8 : 1;
 }
 
 template <int C, int IN, int OUT, bool WGT>
@@ -801,7 +820,8 @@ void k_step(StepArgs a, const int4 *__restrict__ blocks,
     // pair of phase 2, loaded now so it arrives with the gathers.
     // phase 2: tpr lanes per (row, column), or per row and columns of a lane
     // of quad_rows (QR), whose lanes of one row stay within a wavefront
-    constexpr bool QR = Q4 && (OUT == OUT_COMBINE16 || OUT == OUT_TILE32 || OUT == OUT_TILE32H);
+    constexpr bool QR = Q4 && (OUT == OUT_COMBINE16 || OUT == OUT_TILE32 || OUT == OUT_TILE32H ||
+                               OUT == OUT_TILE);
     constexpr int PC = QR ? C / quad_cols<OUT>() : C;
     constexpr int TM0 = QR ? 64 / PC : kBlock / C;
     int tpr = TM0 < 64 ? TM0 : 64;
@@ -1033,22 +1053,46 @@ void k_step(StepArgs a, const int4 *__restrict__ blocks,
     constexpr int LPU = kBlock / GU;
     constexpr int U = 8;  // arcs in flight per lane
     double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    // rounds of unmarked counts as in quad_rows, in 32-bit partials (a lane
+    // takes at most 2^13 arcs); one that met a marked value or a row below the
+    // cut is added arc by arc instead
+    uint32_t p32[4] = {0, 0, 0, 0};
     for (int j0 = sd.y + s; j0 < sd.z; j0 += U * LPU) {
       int u[U];
 #pragma unroll
-      for (int q = 0; q < U; ++q) u[q] = __builtin_nontemporal_load(a.ci + min(j0 + q * LPU, sd.z - 1));
-      uint4 v[U];
+      for (int q = 0; q < U; ++q)
+        u[q] = __builtin_nontemporal_load(a.ci + min(j0 + q * LPU, sd.z - 1));
+      u32x2 x[U];
 #pragma unroll
-      for (int q = 0; q < U; ++q) v[q] = load_quad16<C>(a, u[q], k);
+      for (int q = 0; q < U; ++q)
+        x[q] = *reinterpret_cast<const u32x2 *>(a.Xc16 + (size_t)u[q] * C + 4 * k);
+      uint32_t mx = 0;
+      bool low = false;
 #pragma unroll
       for (int q = 0; q < U; ++q) {
-        const bool ok = j0 + q * LPU < sd.z;
-        acc[0] += ok ? (double)v[q].x : 0.0;
-        acc[1] += ok ? (double)v[q].y : 0.0;
-        acc[2] += ok ? (double)v[q].z : 0.0;
-        acc[3] += ok ? (double)v[q].w : 0.0;
+        if (j0 + q * LPU >= sd.z) x[q] = 0;
+        mx = pk_max16(mx, pk_max16(x[q][0], x[q][1]));
+        low |= u[q] < a.hub;
+      }
+      if (low || (pk_max16(mx, mx >> 16) & 0xffffu) == kC16Hub) {
+#pragma unroll 1
+        for (int j = j0; j < min(j0 + U * LPU, sd.z); j += LPU) {
+          const uint4 v = load_quad16<C>(a, a.ci[j], k);
+          acc[0] += (double)v.x;
+          acc[1] += (double)v.y;
+          acc[2] += (double)v.z;
+          acc[3] += (double)v.w;
+        }
+      } else {
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) p32[i] += half16(x[q][i >> 1], i);
+        }
       }
     }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) acc[i] += (double)p32[i];
     block_colsum_quads<C>(acc, red, a.seg_out + (size_t)(b - n_blocks) * C);
     seg_finish<C, OUT>(a, sd.w, a.seg_out + (size_t)(b - n_blocks) * C);
   } else if constexpr (NP) {
@@ -1298,6 +1342,7 @@ static bool dispatch_multi(int in, int out, const Partition &p, const StepArgs &
     GED_CASE(IN_CNT32, OUT_TILE32)
     GED_CASE(IN_CNT32, OUT_COMBINE32L)
     if constexpr (C >= 4) {  // 16-bit level-2 counts of batch tiles
+      GED_CASE(IN_CNT16, OUT_TILE)
       GED_CASE(IN_CNT16, OUT_TILE32)
       GED_CASE(IN_CNT16, OUT_TILE32H)
       GED_CASE(IN_CNT32, OUT_TILE32H)

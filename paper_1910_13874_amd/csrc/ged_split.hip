@@ -160,7 +160,7 @@ __global__ __launch_bounds__(kBlock) void k_push(const int *__restrict__ rp,
                                                  const int *mcol, int g0, int nc, int C, CT *cnt1,
                                                  CT *cnt2, uint64_t *wl, unsigned *wl_n,
                                                  unsigned wl_cap, uint64_t *wl3, unsigned *wl3_n,
-                                                 unsigned wl3_cap, int h16) {
+                                                 unsigned wl3_cap, int h16, uint16_t *cnt1h) {
   const int64_t jb = offsets[g0], je = offsets[g0 + nc];
   for (int64_t j = jb + blockIdx.x; j < je; j += gridDim.x) {
     const int s = members[j];
@@ -181,6 +181,8 @@ __global__ __launch_bounds__(kBlock) void k_push(const int *__restrict__ rp,
         y = ci[k];
         const size_t o = (size_t)y * C + c;
         const CT old = atomicAdd(&cnt1[o], (CT)1);
+        if (cnt1h)  // two columns to a word: C is even
+          atomicAdd(reinterpret_cast<unsigned *>(cnt1h + (o & ~(size_t)1)), 1u << (16 * (o & 1)));
         if (cnt2) {
           const CT old2 = cnt2_add(cnt2, h16, C, y, c, ds);
           if (!((tmask[y] >> c) & 1ull)) {
@@ -207,6 +209,7 @@ struct MemberFix {
   const int *members = nullptr, *mcol = nullptr;
   int g0 = 0, nc = 0, C = 1;
   CT *cnt1 = nullptr, *cnt2 = nullptr, *lv3 = nullptr;
+  uint16_t *cnt1h = nullptr;
   const double *om3 = nullptr;
   int h16 = -1;  // cnt2 layout
 };
@@ -221,6 +224,7 @@ __device__ __forceinline__ void fix_members(const MemberFix<CT> &f) {
     const int s = f.members[j];
     const size_t o = (size_t)s * f.C + (f.mcol[j] - f.g0);
     f.cnt1[o] = (CT)(f.rp[s + 1] - f.rp[s]);
+    if (f.cnt1h) f.cnt1h[o] = (uint16_t)min((uint32_t)(f.rp[s + 1] - f.rp[s]), kC16Hub);
     if (f.cnt2) cnt2_raise(f.cnt2, f.h16, f.C, s, f.mcol[j] - f.g0, (CT)f.omega2[s]);
     if (f.lv3) f.lv3[o] = (CT)f.om3[s];
   }
@@ -358,7 +362,7 @@ __global__ __launch_bounds__(kBlock) void k_clear_members(const int *__restrict_
                                                           CT *cnt2, CT *lv3,
                                                           unsigned long long *tmask,
                                                           unsigned *wl_n, unsigned *wl3_n,
-                                                          int h16) {
+                                                          int h16, uint16_t *cnt1h) {
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     if (wl_n) *wl_n = 0;
     if (wl3_n) *wl3_n = 0;
@@ -369,6 +373,7 @@ __global__ __launch_bounds__(kBlock) void k_clear_members(const int *__restrict_
     const int c = mcol[j] - g0;
     if (threadIdx.x == 0) {
       cnt1[(size_t)s * C + c] = 0;
+      if (cnt1h) cnt1h[(size_t)s * C + c] = 0;
       if (cnt2) cnt2_zero(cnt2, h16, C, s, c);
       if (lv3) lv3[(size_t)s * C + c] = 0;
       atomicAnd(&tmask[s], ~(1ull << c));
@@ -376,6 +381,7 @@ __global__ __launch_bounds__(kBlock) void k_clear_members(const int *__restrict_
     for (int k = rp[s] + (int)threadIdx.x; k < rp[s + 1]; k += kBlock) {
       const int y = ci[k];
       cnt1[(size_t)y * C + c] = 0;
+      if (cnt1h) cnt1h[(size_t)y * C + c] = 0;
       if (cnt2) cnt2_zero(cnt2, h16, C, y, c);
     }
   }
@@ -871,7 +877,7 @@ void split_fit(ged_graph *g, SplitWs &w, const SplitPlan &pl, int C, size_t wl_n
     w.ws.fit(partition(g, C, false, pl.cut_div));
     // every partition split_dense asks for, built before any capture
     w.ws.fit(step_partition(g, pl, C, IN_CNT32));
-    if (pl.c16_hub >= 0) w.ws.fit(step_partition(g, pl, C, IN_CNT16));
+    if (pl.c16_hub >= 0 || pl.m16) w.ws.fit(step_partition(g, pl, C, IN_CNT16));
     w.ws.fit(final_partition(g, pl, C));
   }
   if (pl.s >= 1) {
@@ -891,6 +897,18 @@ void split_fit(ged_graph *g, SplitWs &w, const SplitPlan &pl, int C, size_t wl_n
       launch_fill_i32(w.wl_n.as<int>(), 0, 1, st);
       w.cnt_bytes = cb;
       w.zero = true;
+    }
+    if (w.cnt2_dirty && !pl.m16) {
+      launch_fill_i32(w.cnt2.as<int>(), 0, w.cnt2.bytes / sizeof(int), st);
+      w.cnt2_dirty = false;
+    }
+    if (pl.m16) {
+      const size_t hb = sizeof(uint16_t) * nC;
+      if (dirty || w.cnt1h.bytes < hb) {
+        w.cnt1h.ensure(hb);
+        launch_fill_i32(w.cnt1h.as<int>(), 0, w.cnt1h.bytes / sizeof(int), st);
+      }
+      w.cnt2h.ensure(hb);
     }
     if (pl.s >= 2 && (wl_need > w.wl_cap || !w.wl.p)) {
       size_t cap = std::max<size_t>(wl_need, 2 * (size_t)w.wl_cap);
@@ -948,9 +966,11 @@ static void push_phase(ged_graph *g, SplitWs &w, const SplitPlan &pl, int C, con
   const int h16 = sizeof(CT) == 4 ? pl.c16_hub : -1;
   hipLaunchKernelGGL(k_push<CT>, dim3(mgrid), dim3(kBlock), 0, st, rp, ci, tmask, offs, mem,
                      mcol, g0, nc, C, c1, c2, w.wl.as<uint64_t>(), w.wl_n.as<unsigned>(),
-                     w.wl_cap, wl3, wl3_n, w.wl3_cap, h16);
+                     w.wl_cap, wl3, wl3_n, w.wl3_cap, h16,
+                     pl.m16 ? w.cnt1h.as<uint16_t>() : nullptr);
   GED_HIP(hipGetLastError());
   MemberFix<CT> fx;
+  fx.cnt1h = pl.m16 ? w.cnt1h.as<uint16_t>() : nullptr;
   fx.rp = rp;
   fx.omega2 = g->omega2.as<const unsigned long long>();
   fx.offsets = offs;
@@ -1020,7 +1040,8 @@ static void clear_phase(ged_graph *g, SplitWs &w, const SplitPlan &pl, int C,
   hipLaunchKernelGGL(k_clear_members<CT>, dim3(mgrid), dim3(kBlock), 0, st, rp, ci, offs, mem,
                      mcol, g0, nc, C, c1, c2, l3, reinterpret_cast<unsigned long long *>(tmask),
                      pl.s >= 2 ? w.wl_n.as<unsigned>() : nullptr,
-                     l3 ? w.wl3_n.as<unsigned>() : nullptr, h16);
+                     l3 ? w.wl3_n.as<unsigned>() : nullptr, h16,
+                     pl.m16 ? w.cnt1h.as<uint16_t>() : nullptr);
   GED_HIP(hipGetLastError());
 }
 
@@ -1061,10 +1082,22 @@ void split_dense(ged_graph *g, SplitWs &w, const SplitPlan &pl, int C, const uin
     a.inj = g->omega2_f.as<const double>();
     a.Xc32 = static_cast<const uint32_t *>(c1);
     a.Y32 = cw.cnt2.as<uint32_t>();
-    if (profile)
+    if (pl.m16) {
+      a.Xc16 = cw.cnt1h.as<const uint16_t>();
+      a.hub = 0;
+      a.Y16 = cw.cnt2h.as<uint16_t>();
+      Partition &pq = step_partition(g, pl, C, IN_CNT16);
+      if (profile)
+        run_step(g, pq, a, IN_CNT16, OUT_TILE32H, st);
+      else
+        launch_step(pq, a, IN_CNT16, OUT_TILE32H, st);
+      a.Xc16 = cw.cnt2h.as<const uint16_t>();  // what level 3 gathers
+      a.Y16 = nullptr;
+    } else if (profile) {
       run_step(g, pn, a, IN_CNT32, OUT_TILE32, st);
-    else
+    } else {
       launch_step(pn, a, IN_CNT32, OUT_TILE32, st);
+    }
     a.Y32 = nullptr;
   }
   // 16-bit level-2 counts: the level-3 gather reads them (IN_CNT16), the
@@ -1090,7 +1123,7 @@ void split_dense(ged_graph *g, SplitWs &w, const SplitPlan &pl, int C, const uin
       a.Xc32 = i == pl.s + 1 ? static_cast<const uint32_t *>(c2) : lv32 + (size_t)(i - 2 - pl.s) * nC;
       // level s+1 gathers the 16-bit level 2 (cut pl.c16_hub), the combining
       // step the 16-bit copy of level a-1 (cut 0, marked values from lv32)
-      const bool g16 = c16 && (i == pl.s + 1 || i == pl.a);
+      const bool g16 = (c16 && (i == pl.s + 1 || i == pl.a)) || (pl.m16 && i == pl.s + 1);
       if (c16 && i == pl.a && i > pl.s + 1) {
         a.Xc16 = w.lv16.as<const uint16_t>();
         a.hub = 0;
@@ -1148,7 +1181,9 @@ void split_dense(ged_graph *g, SplitWs &w, const SplitPlan &pl, int C, const uin
       a.alpha = alpha;
     } else if (i == pl.s + 1) {
       const void *src = pl.s == 1 ? c1 : c2;
-      if (c16) {  // a = 3: the combining step gathers the 16-bit level 2
+      // c16, a = 3: the combining step gathers the 16-bit level 2; m16: level 3
+      // gathers the marked copy
+      if (c16 || (pl.m16 && i < pl.a)) {
         in = IN_CNT16;
         a.Xc32 = static_cast<const uint32_t *>(src);
       } else if (pl.c32) {
@@ -1240,13 +1275,26 @@ bool split_dense2(const ged_graph *g, const SplitPlan &pl, int C, double push2_a
   return push2_arcs * 50.0 > 2.0 * (double)g->nnz * std::max(4.0, 0.57 * C);
 }
 
+// On skewed graphs the gathers of a gathered level 2 are bound by line traffic
+// (R-MAT scale 20, 32 columns: 128 bytes an arc at 8.2 TB/s), so both gather
+// 16-bit copies: a 64-column row is one line.  Level 1 counts members of the
+// group among the neighbours (simple graphs: at most its size), level 2 sums
+// them: both rarely reach 2^16 - 1, whatever omega_2 allows; those that do
+// (member hubs) are marked and read from the 32-bit levels.  250 groups there:
+// 16.3 -> 13.9 ms (its FP64 combining step, half of that, is as before).
+bool split_m16(const ged_graph *g, const SplitPlan &pl, int C, int64_t max_group) {
+  return pl.dense2 && C >= 16 && g->simple && max_group < (int64_t)kC16Max;
+}
+
 void split_tile_clear(ged_graph *g, SplitWs &w, const SplitPlan &pl, int C, const int64_t *offs,
                       const int *mem, const int *mcol, int g0, int nc, int64_t tile_members,
                       uint64_t *tmask, hipStream_t st, bool fill) {
   const int mgrid = grid_for(tile_members, kPushGrid);
   // a gathered level 2 has no worklist to replay
   const bool fill2 = (fill || pl.dense2) && pl.s >= 2 && !pl.push3;
-  if (fill2) {
+  if (fill2 && pl.m16) {
+    w.cnt2_dirty = true;  // written whole by the next tile's step
+  } else if (fill2) {
     const size_t words = (size_t)g->n * C * (pl.c32 ? 1 : 2);
     launch_fill_i32(w.cnt2.as<int>(), 0,
                     pl.c16_hub >= 0 ? (c16_bytes(g->n, pl.c16_hub, C) + 3) / 4 : words, st);

@@ -1492,3 +1492,35 @@ def test_long_rows_finished_in_the_step(ged, kind):
         gg.set_greedy_width(width)
         compare_greedy(gg.greedy(3, alpha, 1e-2), o, (kind, width))
     gg.close()
+
+
+@pytest.mark.parametrize("tile", [16, 64])
+def test_batch_gathered_level2_16bit(ged, tile):
+    """Gathered level-2 tiles of at least 16 columns read 16-bit copies of
+    levels 1 and 2, larger counts marked: a skewed graph whose level 2 exceeds
+    2^16 - 1 (S = V, hub members), long rows, ell* with FP64 and with 32-bit
+    stored levels and none, followed by a batch that pushes its level 2 in the
+    same workspace."""
+    g = inputs.rmat(14, 16, seed=43)
+    gg = ged.GedGraph.from_graph(g)
+    gg.set_batch_tile(tile)
+    gg.set_batch_row_cut(1)
+    alpha = g.default_alpha()
+    by_deg = np.argsort(-g.degrees, kind="stable").astype(np.int32)
+    groups = [np.sort(inputs.group(g.n, 900, 2)), by_deg[:1], np.sort(by_deg[:40]),
+              np.arange(g.n, dtype=np.int32)] + [inputs.group(g.n, 300, 10 + j) for j in range(70)]
+    off = np.concatenate([[0], np.cumsum([len(S) for S in groups])]).astype(np.int64)
+    mem = np.concatenate(groups).astype(np.int32)
+    low = by_deg[g.degrees[by_deg] > 0][-3:]
+    for eps in (3.0, 1e-1, 1e-4):
+        ell = gg.prepare(alpha, eps)[0]
+        say(f"[gathered level 2, 16-bit] tile={tile} ell={ell}")
+        s = gg.score_batch(off, mem, alpha, eps)
+        assert np.array_equal(s, gg.score_batch(off, mem, alpha, eps))
+        for j in (0, 1, 2, 3, 4, 73):
+            c = oracle.score(g, groups[j], alpha, eps)[0]
+            assert rel(s[j], c) <= REL, (eps, j)
+        t = gg.score_batch(np.array([0, 1, 2, 3]), low, alpha, eps)
+        for j in range(3):
+            assert rel(t[j], oracle.score(g, low[j:j + 1], alpha, eps)[0]) <= REL, (eps, j)
+    gg.close()
