@@ -398,6 +398,9 @@ int score_batch(ged_graph *g, const int64_t *offsets, const int32_t *members, in
     }
     b.sw.zero = false;
     b.sw2.zero = false;
+    // the tiles of this call leave level 2 as their steps wrote it, whether
+    // they are enqueued now or replayed from an earlier call's capture
+    if (pl.m16) b.sw.cnt2_dirty = b.sw2.cnt2_dirty = true;
   } else {
     b.X.ensure(sizeof(double) * (size_t)n * C);
     b.Y.ensure(sizeof(double) * (size_t)n * C);

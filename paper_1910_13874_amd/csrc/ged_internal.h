@@ -511,7 +511,10 @@ struct SplitWs {
                          // between tiles
   DBuf lv;               // [nlv*n*C] stored dense levels (double, or uint32 counts)
   DBuf cnt1h, cnt2h;     // [n*C] 16-bit copies of levels 1 (zero between tiles) and 2 (m16)
-  bool cnt2_dirty = false;  // left by gathered level 2, to be zeroed before a push
+  // cnt2 holds a gathered level 2 (m16) and is zeroed before a push; set by
+  // the caller on every launch of such tiles (a replayed capture runs none of
+  // the code that enqueued it)
+  bool cnt2_dirty = false;
   DBuf lv16;             // [n*C] 16-bit copy of the last stored level (16-bit layout)
   DBuf wl, wl_n;         // uint64 worklist [wl_cap], uint32 length
   unsigned wl_cap = 0;

@@ -1292,9 +1292,9 @@ void split_tile_clear(ged_graph *g, SplitWs &w, const SplitPlan &pl, int C, cons
   const int mgrid = grid_for(tile_members, kPushGrid);
   // a gathered level 2 has no worklist to replay
   const bool fill2 = (fill || pl.dense2) && pl.s >= 2 && !pl.push3;
-  if (fill2 && pl.m16) {
-    w.cnt2_dirty = true;  // written whole by the next tile's step
-  } else if (fill2) {
+  // m16: level 2 is written whole by the next such tile's step, and the caller
+  // has marked it (cnt2_dirty) for the first push after them
+  if (fill2 && !pl.m16) {
     const size_t words = (size_t)g->n * C * (pl.c32 ? 1 : 2);
     launch_fill_i32(w.cnt2.as<int>(), 0,
                     pl.c16_hub >= 0 ? (c16_bytes(g->n, pl.c16_hub, C) + 3) / 4 : words, st);
