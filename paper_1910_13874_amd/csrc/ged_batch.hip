@@ -396,11 +396,8 @@ int score_batch(ged_graph *g, const int64_t *offsets, const int32_t *members, in
                             &b.ev_dense[1]})
         GED_HIP(hipEventCreateWithFlags(e, hipEventDisableTiming));
     }
-    b.sw.zero = false;
-    b.sw2.zero = false;
-    // the tiles of this call leave level 2 as their steps wrote it, whether
-    // they are enqueued now or replayed from an earlier call's capture
-    if (pl.m16) b.sw.cnt2_dirty = b.sw2.cnt2_dirty = true;
+    b.sw.state.begin(pl.m16);
+    b.sw2.state.begin(pl.m16);
   } else {
     b.X.ensure(sizeof(double) * (size_t)n * C);
     b.Y.ensure(sizeof(double) * (size_t)n * C);
@@ -494,7 +491,10 @@ int score_batch(ged_graph *g, const int64_t *offsets, const int32_t *members, in
   double *hs = b.h_scores.as<double>();
   GED_HIP(hipMemcpyAsync(hs, b.scores.p, sizeof(double) * (size_t)G, hipMemcpyDeviceToHost, st));
   GED_HIP(hipStreamSynchronize(st));
-  if (split) b.sw.zero = b.sw2.zero = true;
+  if (split) {
+    b.sw.state.end(pl.m16);
+    b.sw2.state.end(pl.m16);
+  }
   std::memcpy(out, hs, sizeof(double) * (size_t)G);
   return GED_OK;
 }

@@ -13,6 +13,7 @@
 #include <vector>
 
 #include "ged.h"
+#include "tile_state.h"
 
 namespace ged {
 
@@ -511,10 +512,6 @@ struct SplitWs {
                          // between tiles
   DBuf lv;               // [nlv*n*C] stored dense levels (double, or uint32 counts)
   DBuf cnt1h, cnt2h;     // [n*C] 16-bit copies of levels 1 (zero between tiles) and 2 (m16)
-  // cnt2 holds a gathered level 2 (m16) and is zeroed before a push; set by
-  // the caller on every launch of such tiles (a replayed capture runs none of
-  // the code that enqueued it)
-  bool cnt2_dirty = false;
   DBuf lv16;             // [n*C] 16-bit copy of the last stored level (16-bit layout)
   DBuf wl, wl_n;         // uint64 worklist [wl_cap], uint32 length
   unsigned wl_cap = 0;
@@ -522,8 +519,7 @@ struct SplitWs {
   unsigned wl3_cap = 0;
   bool lv_zero = false;  // first stored level all zero, as the push needs
   int wl_blocks = 64;    // grid of the worklist kernels (any value is correct)
-  size_t cnt_bytes = 0;  // bytes of the count layout the arrays were zeroed for
-  bool zero = false;
+  TileState state;       // what cnt1, cnt2, wl_n and cnt1h hold between calls
   StepWs ws;
 };
 

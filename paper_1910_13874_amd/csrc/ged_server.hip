@@ -167,7 +167,7 @@ static void lane_setup(Lane &L, int C) {
     L.h_acc.ensure(sizeof(double) * 64);
     launch_fill_i32(L.tmask.as<int>(), 0, (size_t)n * 2, L.st);
     GED_HIP(hipStreamSynchronize(L.st));
-    L.sw.zero = true;
+    L.sw.state.end(false);
     L.bytes = L.tmask.bytes + L.sw.cnt1.bytes + L.sw.cnt2.bytes + L.sw.lv.bytes +
               L.sw.wl.bytes + L.sw.ws.blk.bytes + L.sw.ws.seg.bytes + L.sw.ws.lng.bytes;
     return;
@@ -257,7 +257,7 @@ static void lane_harvest(ged_server *s, Lane &L) {
   if (L.split) {
     for (size_t j = 0; j < L.tile.size(); ++j) emit(s, L.tile[j], GED_OK, acc[j], {}, t);
     L.tile.clear();
-    L.sw.zero = true;
+    L.sw.state.end(false);
     return;
   }
   for (int c = 0; c < L.C; ++c) {
@@ -278,7 +278,7 @@ static bool lane_launch_split(ged_server *s, Lane &L) {
   if (L.pending.empty()) return false;
   ged_graph *g = L.g;
   const int C = L.C;
-  if (!L.sw.zero) split_fit(g, L.sw, L.pl, C, L.sw.wl_cap, L.st);  // after a failed tile
+  if (!L.sw.state.zero()) split_fit(g, L.sw, L.pl, C, L.sw.wl_cap, L.st);  // after a failed tile
   std::vector<int64_t> offs(1, 0);
   std::vector<int> mem, col;
   size_t need = 0;
@@ -322,7 +322,7 @@ static bool lane_launch_split(ged_server *s, Lane &L) {
   const int64_t *d_offs = L.tin.as<const int64_t>();
   const int *d_mem = reinterpret_cast<const int *>(L.tin.as<char>() + ob);
   const int *d_col = d_mem + m;
-  L.sw.zero = false;
+  L.sw.state.begin(false);
   // the narrowest width that holds the tile: a step's cost grows with its
   // width, so a tile of one request on a large graph runs as one column
   int W = 1;
@@ -509,7 +509,7 @@ static void sched_loop(ged_server *s) {
         if (L.split) {
           for (auto &q : L.tile) emit(s, q, err.code, 0.0, {}, t);
           L.tile.clear();
-          L.sw.zero = false;
+          L.sw.state.begin(false);
         } else {
           for (int c = 0; c < L.C; ++c)
             if (L.step[c] > 0) emit(s, L.slot[c], err.code, 0.0, {}, t);

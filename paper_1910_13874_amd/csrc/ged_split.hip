@@ -872,7 +872,7 @@ static bool group_levels_fit32(ged_graph *g, const SplitPlan &pl, const std::vec
 void split_fit(ged_graph *g, SplitWs &w, const SplitPlan &pl, int C, size_t wl_need,
                hipStream_t st, bool counts_only) {
   const size_t nC = (size_t)g->n * C;
-  const bool dirty = !w.zero;
+  const bool dirty = !w.state.zero();
   if (!counts_only) {
     w.ws.fit(partition(g, C, false, pl.cut_div));
     // every partition split_dense asks for, built before any capture
@@ -888,28 +888,28 @@ void split_fit(ged_graph *g, SplitWs &w, const SplitPlan &pl, int C, size_t wl_n
     if (w.cnt1.bytes < cb || w.cnt2.bytes < cb2) {
       w.cnt1.ensure(cb);
       w.cnt2.ensure(cb2);
-      w.zero = false;
+      w.state.counts_replaced();
     }
-    if (!w.zero || w.cnt_bytes != cb) {
-      launch_fill_i32(w.cnt1.as<int>(), 0, w.cnt1.bytes / sizeof(int), st);
-      launch_fill_i32(w.cnt2.as<int>(), 0, w.cnt2.bytes / sizeof(int), st);
+    if (!w.wl_n.p) {
       w.wl_n.ensure(sizeof(unsigned));
-      launch_fill_i32(w.wl_n.as<int>(), 0, 1, st);
-      w.cnt_bytes = cb;
-      w.zero = true;
-    }
-    if (w.cnt2_dirty && !pl.m16) {
-      launch_fill_i32(w.cnt2.as<int>(), 0, w.cnt2.bytes / sizeof(int), st);
-      w.cnt2_dirty = false;
+      w.state.counts_replaced();
     }
     if (pl.m16) {
       const size_t hb = sizeof(uint16_t) * nC;
-      if (dirty || w.cnt1h.bytes < hb) {
+      if (w.cnt1h.bytes < hb) {
         w.cnt1h.ensure(hb);
-        launch_fill_i32(w.cnt1h.as<int>(), 0, w.cnt1h.bytes / sizeof(int), st);
+        w.state.copy_replaced();
       }
       w.cnt2h.ensure(hb);
     }
+    const TileState::Fill fill = w.state.fit(cb, pl.m16);
+    if (fill.counts) {
+      launch_fill_i32(w.cnt1.as<int>(), 0, w.cnt1.bytes / sizeof(int), st);
+      launch_fill_i32(w.cnt2.as<int>(), 0, w.cnt2.bytes / sizeof(int), st);
+      launch_fill_i32(w.wl_n.as<int>(), 0, 1, st);
+    }
+    if (fill.level2) launch_fill_i32(w.cnt2.as<int>(), 0, w.cnt2.bytes / sizeof(int), st);
+    if (fill.copy) launch_fill_i32(w.cnt1h.as<int>(), 0, w.cnt1h.bytes / sizeof(int), st);
     if (pl.s >= 2 && (wl_need > w.wl_cap || !w.wl.p)) {
       size_t cap = std::max<size_t>(wl_need, 2 * (size_t)w.wl_cap);
       cap = std::min<size_t>(cap, 0xffffffffu);
@@ -1292,8 +1292,8 @@ void split_tile_clear(ged_graph *g, SplitWs &w, const SplitPlan &pl, int C, cons
   const int mgrid = grid_for(tile_members, kPushGrid);
   // a gathered level 2 has no worklist to replay
   const bool fill2 = (fill || pl.dense2) && pl.s >= 2 && !pl.push3;
-  // m16: level 2 is written whole by the next such tile's step, and the caller
-  // has marked it (cnt2_dirty) for the first push after them
+  // m16: level 2 is written whole by the next such tile's step, and zeroed
+  // before the first push after them (TileState)
   if (fill2 && !pl.m16) {
     const size_t words = (size_t)g->n * C * (pl.c32 ? 1 : 2);
     launch_fill_i32(w.cnt2.as<int>(), 0,
@@ -1461,7 +1461,7 @@ int split_score(ged_graph *g, const int32_t *S, int32_t s_len, double *out) {
     split_tile_clear(g, w, pl, 1, d_offs, d_mem, d_mcol, 0, 1, cap, tm, st);
   };
   if (!g->score_done) GED_HIP(hipEventCreateWithFlags(&g->score_done, hipEventDisableTiming));
-  w.zero = false;
+  w.state.begin(false);
   try {
     if (g->prof.on) {
       enqueue_main();
@@ -1496,7 +1496,7 @@ int split_score(ged_graph *g, const int32_t *S, int32_t s_len, double *out) {
     g->split_tmask_ready = false;  // member bits may be left set
     throw;
   }
-  w.zero = true;  // the clean-up is queued ahead of any later work on the stream
+  w.state.end(false);  // the clean-up is queued ahead of any later work on the stream
   // a dense first stored level leaves its values; the pushed one is cleared
   if (pl.nlv > 0) w.lv_zero = pl.push3;
   GED_HIP(hipEventSynchronize(g->score_done));
