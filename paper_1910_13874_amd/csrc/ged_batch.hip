@@ -462,6 +462,7 @@ int score_batch(ged_graph *g, const int64_t *offsets, const int32_t *members, in
                                    (const void *)(intptr_t)pl.m16, b.sw.cnt1h.p, b.sw.cnt2h.p,
                                    b.sw2.cnt1h.p, b.sw2.cnt2h.p};
 
+  b.tmask_ready = b.tmask2_ready = false;  // a call that fails may leave member bits
   if (g->prof.on) {
     // profiling times every step launch with events: run the batch eagerly
     enqueue();
@@ -491,7 +492,9 @@ int score_batch(ged_graph *g, const int64_t *offsets, const int32_t *members, in
   double *hs = b.h_scores.as<double>();
   GED_HIP(hipMemcpyAsync(hs, b.scores.p, sizeof(double) * (size_t)G, hipMemcpyDeviceToHost, st));
   GED_HIP(hipStreamSynchronize(st));
+  b.tmask_ready = true;
   if (split) {
+    b.tmask2_ready = true;
     b.sw.state.end(pl.m16);
     b.sw2.state.end(pl.m16);
   }
