@@ -294,7 +294,7 @@ int prepare(ged_graph *g, double alpha, double eps) {
   hipStream_t st = g->stream;
   const int64_t n = g->n;
   Partition &p = partition(g, 1);
-  g->pws.fit(p);
+  g->pws.fit(p, st);
   pc.valid = false;
   pc.tr_r = -1;
   pc.W.clear();
@@ -349,7 +349,7 @@ void t_levels_to(ged_graph *g, int L) {
   hipStream_t st = g->stream;
   const int64_t n = g->n;
   Partition &p = partition(g, 1);
-  g->pws.fit(p);
+  g->pws.fit(p, st);
   const size_t need = sizeof(double) * (size_t)n * (size_t)(L - pc.ell);
   if (pc.t_ext.bytes < need) {
     DBuf nb;
@@ -386,7 +386,7 @@ double walk_total(ged_graph *g, int ell) {
   hipStream_t st = g->stream;
   const int64_t n = g->n;
   Partition &p = partition(g, 1);
-  g->pws.fit(p);
+  g->pws.fit(p, st);
   pc.t_tail[0].ensure(sizeof(double) * n);
   pc.t_tail[1].ensure(sizeof(double) * n);
   if (pc.tail_level < 0) {
@@ -467,7 +467,7 @@ static void ensure_score_buffers(ged_graph *g, int s_len, hipStream_t st) {
   g->acc.ensure(sizeof(double) * 64);
   g->s_levels.ensure(sizeof(double) * (size_t)(g->prep.ell + 2));
   g->out_host.ensure(64, hipHostMallocCoherent);
-  g->sws.fit(partition(g, 1));
+  g->sws.fit(partition(g, 1), st);
   if (s_len > g->s_cap) {
     int cap = std::max(256, g->s_cap);
     while (cap < s_len) cap *= 2;
@@ -483,11 +483,12 @@ static std::vector<const void *> score_signature(ged_graph *g) {
   double a = pc.alpha;
   const void *abits;
   std::memcpy(&abits, &a, sizeof(a));
-  return {g->mask.p, g->vec[0].p, g->vec[1].p, g->acc.p, g->s_levels.p, g->s_dev.p,
-          g->sws.blk.p, g->sws.seg.p, g->sws.lng.p, g->sws.red2.p, pc.t_levels.p,
-          (const void *)g->stream,
-          abits, (const void *)(intptr_t)pc.ell, (const void *)(intptr_t)g->s_cap,
-          (const void *)(intptr_t)0 /* level-by-level chain */};
+  std::vector<const void *> sig = {
+      g->mask.p, g->vec[0].p, g->vec[1].p, g->acc.p, g->s_levels.p, g->s_dev.p, pc.t_levels.p,
+      (const void *)g->stream, abits, (const void *)(intptr_t)pc.ell,
+      (const void *)(intptr_t)g->s_cap};
+  g->sws.key(sig);
+  return sig;
 }
 
 // One group of a small graph: passed as arguments or staged in coherent host

@@ -127,7 +127,7 @@ static int autotune_tile(ged_graph *g, BatchWs &b) {
   auto timed = [&](int C, int cut) -> double {
     Partition &p = partition(g, C, false, cut);
     StepWs ws;
-    ws.fit(p);
+    ws.fit(p, st);
     b.X.ensure(sizeof(double) * (size_t)n * C);
     b.Y.ensure(sizeof(double) * (size_t)n * C);
     launch_fill_f64(b.X.as<double>(), 0.0, (size_t)n * C, st);
@@ -312,7 +312,7 @@ int score_batch(ged_graph *g, const int64_t *offsets, const int32_t *members, in
   pl.cut_div = g->batch_cut_div;
   if (split) pl.c16_hub = split_c16_hub(g, pl, C, st);
   g->c16_used = pl.c16_hub;
-  b.ws.fit(partition(g, C, false, g->batch_cut_div));
+  b.ws.fit(partition(g, C, false, g->batch_cut_div), st);
   // internal ids, duplicates inside a group dropped; column of every member
   std::vector<int64_t> &hoff = b.h_offsets;
   std::vector<int> &hmem = b.h_members;
@@ -443,12 +443,11 @@ int score_batch(ged_graph *g, const int64_t *offsets, const int32_t *members, in
   std::memcpy(&abits, &abits_d, sizeof(abits));
   std::vector<const void *> sig = {b.tmask.p,      b.X.p,       b.Y.p,
                                    b.offsets.p,    b.members.p, b.mcol.p,   b.scores.p,
-                                   b.ws.blk.p,     b.ws.seg.p,  b.ws.lng.p, b.ws.red2.p,
                                    b.sw.cnt1.p,    b.sw.cnt2.p, b.sw.lv.p,  b.sw.wl.p,
-                                   b.sw.wl_n.p,    b.sw.ws.blk.p, b.sw.ws.seg.p, b.sw.ws.lng.p,
+                                   b.sw.wl_n.p,
                                    b.sw2.cnt1.p,   b.sw2.cnt2.p, b.sw2.wl.p,   b.sw2.wl_n.p,
                                    b.tmask2.p,     (const void *)b.side,
-                                   b.sw.ws.red2.p, g->omega2.p, g->omega_lv.p, g->prep.tr.p,
+                                   g->omega2.p, g->omega_lv.p, g->prep.tr.p,
                                    g->prep.t_levels.p, (const void *)st, abits,
                                    (const void *)(uintptr_t)b.sw.wl_cap,
                                    (const void *)(uintptr_t)b.sw2.wl_cap,
@@ -461,6 +460,8 @@ int score_batch(ged_graph *g, const int64_t *offsets, const int32_t *members, in
                                    (const void *)(intptr_t)pl.dense2, g->omega2_f.p, g->ci_l.p,
                                    (const void *)(intptr_t)pl.m16, b.sw.cnt1h.p, b.sw.cnt2h.p,
                                    b.sw2.cnt1h.p, b.sw2.cnt2h.p};
+  b.ws.key(sig);
+  b.sw.ws.key(sig);
 
   b.tmask_ready = b.tmask2_ready = false;  // a call that fails may leave member bits
   if (g->prof.on) {

@@ -656,10 +656,6 @@ int greedy_width_for(const ged_graph *g) {
   return g->nnz <= kSmallArcs ? kWidthSmall : kWidthFirst;
 }
 
-static size_t step_ws_bytes(const StepWs &w) {
-  return w.blk.bytes + w.seg.bytes + w.lng.bytes + w.red2.bytes + w.cnt.bytes;
-}
-
 size_t greedy_bytes_held(const ged_graph *g) {
   size_t b = g->prep.t_ext.bytes + g->prep.t_tail[0].bytes + g->prep.t_tail[1].bytes;
   std::lock_guard<std::mutex> lk(g_greedy_mu);
@@ -671,7 +667,7 @@ size_t greedy_bytes_held(const ged_graph *g) {
                         &c.dc32, &c.wl2, &c.wl2_n, &c.X, &c.Y, &c.cand_dev, &c.gains,
                         &c.topk_k[0], &c.topk_k[1], &c.topk_i[0], &c.topk_i[1]})
     b += d->bytes;
-  return b + step_ws_bytes(c.ws1) + step_ws_bytes(c.ws1r) + step_ws_bytes(c.wsC);
+  return b + c.ws1.bytes() + c.ws1r.bytes() + c.wsC.bytes();
 }
 
 // Upper bound of the device bytes a greedy run of k picks whose walk length
@@ -710,7 +706,7 @@ size_t greedy_footprint(ged_graph *g, int ell_max, int k) {
   // source-bucketed ones)
   size_t parts = 0;
   auto fields = [&parts](const Partition &p, size_t *f) {
-    parts += p.device_bytes() + sizeof(unsigned) * (size_t)(p.n_long + 64);  // and its counters
+    parts += p.device_bytes();
     f[0] = std::max(f[0], 8 * (size_t)std::max(1, p.n_blocks) * p.C);
     f[1] = std::max(f[1], 8 * (size_t)std::max(1, p.n_segs) * p.C);
     f[2] = std::max(f[2], 8 * (size_t)std::max(1, p.n_long) * p.C);
@@ -724,7 +720,7 @@ size_t greedy_footprint(ged_graph *g, int ell_max, int k) {
     if (split && !g->weighted) fields(partition_narrow(g, C), fc);
   }
   for (int i = 0; i < 4; ++i) b += f1[i] + fr[i] + fc[i];
-  b += parts;
+  b += parts + 3 * sizeof(unsigned) * kInlineFixSegs;  // and the segment counters
   // total-walk levels beyond ell* (the bounds read them up to ell on
   // undirected graphs): the buffer doubles, and the old one is copied
   // before it is freed; the two chain vectors of the level sums
@@ -783,7 +779,7 @@ static void miss_chains(GreedyCtx &c, int ell) {
     const bool rev = dir == 1;
     Partition &p = partition(g, 1, rev);
     StepWs &ws = rev ? c.ws1r : c.ws1;
-    ws.fit(p);
+    ws.fit(p, c.st);
     double *L = (rev ? c.b_levels : c.m_levels).as<double>();
     int i0 = 1;
     if (c.split && !g->weighted) {  // level 1 from the S-arc counts
@@ -1005,7 +1001,7 @@ static void eval_batch(GreedyCtx &c, const int *cand, int nc, int Cb, int ell, i
     c.layout_C = C;
   }
   Partition &p = partition(g, C);
-  c.wsC.fit(p);
+  c.wsC.fit(p, c.st);
   if (nc > 64) throw HipError{GED_ERR_ARG, "candidate batch larger than 64"};
   // Level 2 of 32-bit gain chains by a push from the level-1 vertices when
   // the arcs it adds along are few: at most sum_x (omega_2(x) + deg(x)) <=
@@ -1113,7 +1109,7 @@ static void eval_batch(GreedyCtx &c, const int *cand, int nc, int Cb, int ell, i
     a.accum = 0;
     if (g32) {
       Partition &pn = partition_narrow(g, C);
-      c.wsC.fit(pn);
+      c.wsC.fit(pn, c.st);
       c.wsC.into(a);
       pr = &pn;
       // the candidates' injected miss counts were written by k_cand_put
@@ -1177,7 +1173,7 @@ static void eval_batch(GreedyCtx &c, const int *cand, int nc, int Cb, int ell, i
       uint32_t *dc = nullptr;
       const double al = g->prep.alpha;
       if (p32) {
-        c.wsC.fit(pn);
+        c.wsC.fit(pn, c.st);
         c.wsC.into(a);
         c.dc32.ensure(2 * sizeof(uint32_t) * nC);
         dc = c.dc32.as<uint32_t>();

@@ -419,20 +419,29 @@ __host__ __device__ constexpr int gather_units(int C, int in_mode, bool weighted
 void launch_fill_i32(int *p, int v, size_t count, hipStream_t st);
 
 // Partial-sum buffers of one step stream (each path owns its own, so captured
-// graphs never see a buffer another path reallocated).
+// graphs never see a buffer another path reallocated; key() is what a graph
+// captured from steps on it depends on).  cnt: the segment counters of
+// seg_finish, of one size for every partition that uses them and zeroed on the
+// steps' stream.
 struct StepWs {
   DBuf blk, seg, lng, red2, cnt;
-  void fit(const Partition &p) {
+  void fit(const Partition &p, hipStream_t st) {
     blk.ensure(sizeof(double) * (size_t)(p.n_blocks > 0 ? p.n_blocks : 1) * p.C);
     seg.ensure(sizeof(double) * (size_t)(p.n_segs > 0 ? p.n_segs : 1) * p.C);
     lng.ensure(sizeof(double) * (size_t)(p.n_long > 0 ? p.n_long : 1) * p.C);
     red2.ensure(sizeof(double) * (size_t)kReduceBlocks * p.C);
-    if (p.n_long > 0 && cnt.bytes < sizeof(unsigned) * (size_t)p.n_long) {
-      cnt.ensure(sizeof(unsigned) * (size_t)p.n_long);
-      launch_fill_i32(cnt.as<int>(), 0, cnt.bytes / sizeof(int), nullptr);
-      GED_HIP(hipStreamSynchronize(nullptr));
+    if (p.n_long > 0 && p.n_segs <= kInlineFixSegs && !cnt.p) {  // n_long <= n_segs
+      DBuf c;  // kept once its fill is launched
+      c.ensure(sizeof(unsigned) * kInlineFixSegs);
+      launch_fill_i32(c.as<int>(), 0, kInlineFixSegs, st);
+      std::swap(cnt.p, c.p);
+      std::swap(cnt.bytes, c.bytes);
     }
   }
+  void key(std::vector<const void *> &k) const {
+    k.insert(k.end(), {blk.p, seg.p, lng.p, red2.p, cnt.p});
+  }
+  size_t bytes() const { return blk.bytes + seg.bytes + lng.bytes + red2.bytes + cnt.bytes; }
   double *scratch() const { return red2.as<double>(); }
   void into(StepArgs &a) const {
     a.blk_part = blk.as<double>();

@@ -38,7 +38,7 @@ namespace ged {
 int greedy_run(ged_graph *g, int32_t k, double alpha, double eps, double eta, uint64_t seed,
                bool stochastic, int32_t *out_group, double *out_score, ged_greedy_trace *tr,
                const std::atomic<int> *stop);
-void split_fit_width(ged_graph *g, SplitWs &w, const SplitPlan &pl, int C);
+void split_fit_width(ged_graph *g, SplitWs &w, const SplitPlan &pl, int C, hipStream_t st);
 
 static double now_us() {
   using namespace std::chrono;
@@ -141,8 +141,10 @@ static void lane_setup(Lane &L, int C) {
   ged_graph *g = L.g;
   const int64_t n = g->n;
   L.C = C;
+  GED_HIP(hipStreamCreateWithFlags(&L.st, hipStreamNonBlocking));
+  GED_HIP(hipEventCreateWithFlags(&L.ev, hipEventDisableTiming));
   Partition &p = partition(g, C);
-  L.ws.fit(p);
+  L.ws.fit(p, L.st);
   // everything the greedy path may need, so no partition is built while the
   // lane runs on another thread
   partition(g, 1);
@@ -152,8 +154,6 @@ static void lane_setup(Lane &L, int C) {
   if (split_ok(g)) {
     L.split = true;
     L.pl = split_plan(g, g->prep.ell);
-    GED_HIP(hipStreamCreateWithFlags(&L.st, hipStreamNonBlocking));
-    GED_HIP(hipEventCreateWithFlags(&L.ev, hipEventDisableTiming));
     split_tables(g, L.pl, L.st);  // per-graph tables now, not while greedy runs
     if (L.pl.s >= 2) L.om2 = omega2_host(g, L.st);
     // worklist: a tile holds requests while their needs (<= n + nnz/512 + 1
@@ -161,7 +161,7 @@ static void lane_setup(Lane &L, int C) {
     const size_t cap = (size_t)C * split_wl_need(g, 0) + 2 * (size_t)n;
     split_fit(g, L.sw, L.pl, C, cap, L.st);
     // a tile runs at the narrowest power-of-two width that holds its requests
-    for (int w = 1; w < C; w *= 2) split_fit_width(g, L.sw, L.pl, w);
+    for (int w = 1; w < C; w *= 2) split_fit_width(g, L.sw, L.pl, w, L.st);
     L.tmask.ensure(sizeof(uint64_t) * (size_t)n);
     L.acc.ensure(sizeof(double) * 64);
     L.h_acc.ensure(sizeof(double) * 64);
@@ -179,8 +179,6 @@ static void lane_setup(Lane &L, int C) {
   L.state.ensure(sizeof(int) * 128);
   L.h_state.ensure(sizeof(int) * 128);
   L.h_acc.ensure(sizeof(double) * 64);
-  GED_HIP(hipStreamCreateWithFlags(&L.st, hipStreamNonBlocking));
-  GED_HIP(hipEventCreateWithFlags(&L.ev, hipEventDisableTiming));
   launch_fill_f64(L.X.as<double>(), 0.0, (size_t)n * C, L.st);
   launch_fill_f64(L.Y.as<double>(), 0.0, (size_t)n * C, L.st);
   launch_fill_i32(L.tmask.as<int>(), 0, (size_t)n * 2, L.st);

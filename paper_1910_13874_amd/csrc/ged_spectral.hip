@@ -94,9 +94,9 @@ double sigma_max(ged_graph *g) {
   Partition &pf = partition(g, 1);
   Partition &pr = partition(g, 1, directed);
   StepWs ws;
-  ws.fit(pf);
+  ws.fit(pf, st);
   StepWs wsr;
-  wsr.fit(pr);
+  wsr.fit(pr, st);
   DBuf x, y, z, part, cw, mz;
   x.ensure(sizeof(double) * (size_t)n);
   y.ensure(sizeof(double) * (size_t)n);

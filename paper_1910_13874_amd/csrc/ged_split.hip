@@ -874,11 +874,11 @@ void split_fit(ged_graph *g, SplitWs &w, const SplitPlan &pl, int C, size_t wl_n
   const size_t nC = (size_t)g->n * C;
   const bool dirty = !w.state.zero();
   if (!counts_only) {
-    w.ws.fit(partition(g, C, false, pl.cut_div));
+    w.ws.fit(partition(g, C, false, pl.cut_div), st);
     // every partition split_dense asks for, built before any capture
-    w.ws.fit(step_partition(g, pl, C, IN_CNT32));
-    if (pl.c16_hub >= 0 || pl.m16) w.ws.fit(step_partition(g, pl, C, IN_CNT16));
-    w.ws.fit(final_partition(g, pl, C));
+    w.ws.fit(step_partition(g, pl, C, IN_CNT32), st);
+    if (pl.c16_hub >= 0 || pl.m16) w.ws.fit(step_partition(g, pl, C, IN_CNT16), st);
+    w.ws.fit(final_partition(g, pl, C), st);
   }
   if (pl.s >= 1) {
     const size_t cb = (pl.c32 ? sizeof(uint32_t) : sizeof(uint64_t)) * nC;
@@ -944,11 +944,11 @@ void split_fit(ged_graph *g, SplitWs &w, const SplitPlan &pl, int C, size_t wl_n
 // Partitions and partial buffers for tiles of width C in a workspace whose
 // counts were fitted for a wider tile: the counts, levels and worklists of a
 // narrower tile use the first n * C entries of the same buffers.
-void split_fit_width(ged_graph *g, SplitWs &w, const SplitPlan &pl, int C) {
-  w.ws.fit(partition(g, C, false, pl.cut_div));
-  w.ws.fit(step_partition(g, pl, C, IN_CNT32));
-  if (pl.c16_hub >= 0) w.ws.fit(step_partition(g, pl, C, IN_CNT16));
-  w.ws.fit(final_partition(g, pl, C));
+void split_fit_width(ged_graph *g, SplitWs &w, const SplitPlan &pl, int C, hipStream_t st) {
+  w.ws.fit(partition(g, C, false, pl.cut_div), st);
+  w.ws.fit(step_partition(g, pl, C, IN_CNT32), st);
+  if (pl.c16_hub >= 0) w.ws.fit(step_partition(g, pl, C, IN_CNT16), st);
+  w.ws.fit(final_partition(g, pl, C), st);
 }
 
 template <class CT>
@@ -1473,13 +1473,13 @@ int split_score(ged_graph *g, const int32_t *S, int32_t s_len, double *out) {
       std::memcpy(&abits, &ab, sizeof(ab));
       std::vector<const void *> sig = {
           g->split_tmask.p, w.cnt1.p, w.cnt2.p, w.lv.p, w.wl.p, w.wl_n.p, w.wl3.p, w.wl3_n.p,
-          (const void *)(uintptr_t)w.wl3_cap, (const void *)(intptr_t)pl.push3, w.ws.blk.p, w.ws.seg.p,
-          w.ws.lng.p, w.ws.red2.p, g->split_in.p, g->split_in_host.p, (const void *)(intptr_t)staged,
+          (const void *)(uintptr_t)w.wl3_cap, (const void *)(intptr_t)pl.push3, g->split_in.p, g->split_in_host.p, (const void *)(intptr_t)staged,
           g->prep.t_levels.p, g->prep.tr.p, g->omega2.p,
           g->omega_lv.p, g->out_host.p, (const void *)st, abits, (const void *)(intptr_t)g->prep.ell,
           (const void *)(intptr_t)cap, (const void *)(uintptr_t)w.wl_cap,
           (const void *)(intptr_t)1 /* split */, (const void *)(intptr_t)pl.lv32,
           (const void *)(intptr_t)pl.dense2, g->omega2_f.p, g->ci_l.p};
+      w.ws.key(sig);
       SplitExec &x = g->split_exec[(pl.push3 ? 1 : 0) + (staged ? 2 : 0) + (pl.lv32 ? 4 : 0) +
                                    (pl.dense2 ? 8 : 0)];
       if (x.exec && sig != x.sig) x.drop();

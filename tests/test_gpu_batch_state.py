@@ -90,3 +90,39 @@ def test_pushed_batch_after_replayed_gathered_batch(ged, tile):
         p.run_heavy()
         p.run_light()
     p.gg.close()
+
+
+@pytest.mark.parametrize("kind", ["directed", "undirected"])
+def test_captured_batch_after_wider_long_rows(ged, kind):
+    """A captured batch is replayed after profiled (eager) batches at narrower
+    tiles and lower row-split thresholds, whose partitions have more long rows:
+    the long rows' counters are those it was captured with."""
+    n = 60_000
+    hubs = [(h, 140 + 90 * h) for h in range(60)] + [(60, 9000), (61, 50_000)]
+    r = inputs.uniform_ints(2 * 40_000, n, 5).astype(np.int32)
+    src = np.concatenate([r[0::2]] + [np.arange(100, 100 + d, dtype=np.int32) for _, d in hubs])
+    dst = np.concatenate([r[1::2]] + [np.full(d, h, np.int32) for h, d in hubs])
+    g = inputs.from_edges(n, src, dst, symmetrize=kind != "directed")
+    gg = ged.GedGraph.from_graph(g)
+    alpha, eps = 0.5 * oracle.default_alpha(g, None), 1e-3
+    groups = [inputs.group(n, 5, 1), np.array([60], np.int32), np.array([0, 30, 61], np.int32),
+              inputs.group(n, 300, 2)] * 17
+    off, mem = flat(groups)
+    want = [oracle.score(g, S, alpha, eps)[0] for S in groups[:4]]
+
+    def batch(tile, cut, profiled=False):
+        gg.set_batch_tile(tile)
+        gg.set_batch_row_cut(cut)
+        gg.profile_enable(profiled)
+        s = gg.score_batch(off, mem, alpha, eps)
+        gg.profile_enable(False)
+        assert max(rel(x, want[j % 4]) for j, x in enumerate(s)) <= REL, (tile, cut)
+        return s
+
+    first = batch(64, 1)
+    for tile, cut in ((32, 4), (16, 4), (8, 1)):
+        batch(tile, cut, True)
+        assert np.array_equal(batch(64, 1), first)
+    s = gg.score(groups[3], alpha, eps)
+    assert rel(s, want[3]) <= REL and gg.score(groups[3], alpha, eps) == s
+    gg.close()
