@@ -126,3 +126,35 @@ def test_captured_batch_after_wider_long_rows(ged, kind):
     s = gg.score(groups[3], alpha, eps)
     assert rel(s, want[3]) <= REL and gg.score(groups[3], alpha, eps) == s
     gg.close()
+
+
+def test_captured_16bit_batch_after_wider_copy(ged):
+    """A batch in the 16-bit layout with two stored levels is replayed after a
+    profiled batch at twice the width with one stored level: the same bytes of
+    stored levels, but a larger 16-bit copy, which the capture has to follow."""
+    g = inputs.erdos_renyi(30_000, 120_000, 11)
+    gg = ged.GedGraph.from_graph(g)
+    gg.set_count16(0)
+    alpha = 0.4 / g.max_degree
+    eps_of = {}
+    for e in range(80):
+        eps = 10.0 ** (4 - 0.25 * e)
+        eps_of.setdefault(gg.prepare(alpha, eps)[0], eps)
+    groups = [inputs.group(g.n, 3 + 5 * j, j) for j in range(20)]
+    off, mem = flat(groups)
+
+    def batch(tile, ell, profiled=False):
+        gg.set_batch_tile(tile)
+        gg.set_batch_row_cut(1)
+        gg.profile_enable(profiled)
+        s = gg.score_batch(off, mem, alpha, eps_of[ell])
+        gg.profile_enable(False)
+        assert gg.count16_hub() == 0
+        for j in (0, 7, 19):
+            assert rel(s[j], oracle.score(g, groups[j], alpha, eps_of[ell])[0]) <= REL
+        return s
+
+    first = batch(8, 10)
+    batch(16, 8, True)
+    assert np.array_equal(batch(8, 10), first)
+    gg.close()
