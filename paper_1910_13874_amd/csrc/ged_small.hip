@@ -37,6 +37,7 @@ constexpr int kSmallChunk = 32;    // most arcs of a chunk
 constexpr int kSmallTinyChunk = 16;            // ... of a graph of at most
 constexpr int64_t kSmallTinyArcs = 32 << 10;   // this many arcs
 constexpr size_t kSmallLds = 160 * 1024 - 1024;
+constexpr int kSmallGrid = 1 << 20;  // groups per launch (a grid holds fewer than 2^32 threads)
 
 // One direction of a small graph in slices.
 struct SmallSide {
@@ -530,12 +531,15 @@ void small_scores(ged_graph *g, const int64_t *offs, const int *mem, int groups,
   else
     a.mem = mem;
   a.n_inline = n_inline;
-  a.offs = offs;
-  a.out = out;
-  if (g->weighted)
-    small_run<true>(sg, &a, kScoreChain, groups, st);
-  else
-    small_run<false>(sg, &a, kScoreChain, groups, st);
+  for (int g0 = 0; g0 < groups; g0 += kSmallGrid) {
+    const int grid = std::min(groups - g0, kSmallGrid);
+    a.offs = offs ? offs + g0 : nullptr;
+    a.out = out + g0;
+    if (g->weighted)
+      small_run<true>(sg, &a, kScoreChain, grid, st);
+    else
+      small_run<false>(sg, &a, kScoreChain, grid, st);
+  }
 }
 
 void small_miss(ged_graph *g, int levels, int r, uint32_t *smask, int join, double *M, double *Mb,

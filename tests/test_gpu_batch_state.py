@@ -158,3 +158,18 @@ def test_captured_16bit_batch_after_wider_copy(ged):
     batch(16, 8, True)
     assert np.array_equal(batch(8, 10), first)
     gg.close()
+
+
+def test_more_groups_than_one_launch(ged):
+    """A batch on a small graph with more groups than one launch of a workgroup
+    each takes (2^22 groups are 2^32 threads): every score is that of its
+    group, whichever launch it fell into."""
+    g = inputs.erdos_renyi(40, 90, 3)
+    gg = ged.GedGraph.from_graph(g)
+    alpha, eps = g.default_alpha(), 1e-2
+    G = (1 << 22) + 1000
+    mem = (np.arange(G, dtype=np.int64) * 7 % g.n).astype(np.int32)
+    s = gg.score_batch(np.arange(G + 1, dtype=np.int64), mem, alpha, eps)
+    one = np.array([oracle.score(g, np.array([v], np.int32), alpha, eps)[0] for v in range(g.n)])
+    assert (np.abs(s - one[mem]) <= REL * one[mem]).all()  # isolated vertices score 0
+    gg.close()
