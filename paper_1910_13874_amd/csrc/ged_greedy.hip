@@ -1327,7 +1327,7 @@ int greedy_run(ged_graph *g, int32_t k, double alpha, double eps, double eta, ui
   c.fixed = g->greedy_width;
   c.C = c.fixed ? c.fixed : kWidthMax;
   c.split = split_ok(g);
-  c.small = !g->prof.on && small_score_ok(g);
+  c.small = !g->prof.on && small_greedy_ok(g);
   c.join = -1;
   c.evals = 0;
   c.rounds = 0;

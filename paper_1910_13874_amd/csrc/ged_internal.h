@@ -827,13 +827,31 @@ int split_score(ged_graph *g, const int32_t *S, int32_t s_len, double *out);
 // are 16-bit ids and one vertex vector takes at most the CU's LDS.  A batch
 // pays up to 128 K arcs (n = 10^4, 80 K arcs, 256 groups: 700 us in tiles, 150
 // us so; below that the tile path costs a launch chain whatever its size).
-// A single group, one workgroup on one CU, up to 40 K (a level of 80 K arcs
-// takes it 6 us, a step 4 to 5).
+// A batch of at most 64 groups is one tile: the chain wins by the tile's
+// launches, and loses where a level of one group costs more than they do --
+// weighted arcs (10 bytes each) on the widest graphs (n = 18,000, 127 K arcs,
+// 64 groups: 258 us, in a tile 216; 79 K arcs: 193 and 293) and the widest
+// directed ones (n = 18,000, 40 K arcs, 64 groups: 198 and 181).
+//
+// A single group, one workgroup on one CU, pays up to 40 K arcs (a level of
+// 80 K takes it 6 us, a step 4 to 5) and while its level is not held up by the
+// passes over the rows: ER, 20 K and 40 K arcs, n = 9,000: 54 and 69 us
+// against 65 and 71 by steps, n = 12,000: 66 and 87 against 62 and 71,
+// n = 18,000: 110 and 122 against 67 and 69; with weights n = 5,000: 60
+// against 65, n = 7,000: 63 against 60 (40 K arcs).  A greedy round saves host
+// waits too: n = 9,000 929 and 1,367 us against 1,238 and 1,742, n = 12,000
+// 1,278 and 1,400 against 1,234 and 1,268, n = 18,000 1,763 against 1,248.
 constexpr int64_t kSmallVertices = 18000;
 constexpr int64_t kSmallBatchArcs = 128 << 10;
+constexpr int kSmallFewGroups = 64;
+constexpr int64_t kSmallFewWeighted = 14336, kSmallFewWeightedArcs = 96 << 10;
+constexpr int64_t kSmallFewDirected = 16384;
 constexpr int64_t kSmallScoreArcs = 40 << 10;
-bool small_batch_ok(ged_graph *g);
+constexpr int64_t kSmallScoreVertices = 8192, kSmallScoreWeighted = 6144;
+constexpr int64_t kSmallGreedyVertices = 10240;
+bool small_batch_ok(ged_graph *g, int groups);
 bool small_score_ok(ged_graph *g);
+bool small_greedy_ok(ged_graph *g);
 // Scores of groups (members mem[offs[g] .. offs[g+1]), internal ids; device
 // or coherent host memory) to out[groups], for the prepared (alpha, eps).
 // n_inline >= 0: one group, whose n_inline <= kSmallInline members mem (host)

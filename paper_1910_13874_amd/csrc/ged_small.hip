@@ -33,6 +33,7 @@ namespace ged {
 constexpr int kSmallThreads = 1024;
 constexpr int kSmallWaves = kSmallThreads / 64;
 constexpr int kSmallPasses = 18;   // most slices per wavefront (two registers each)
+constexpr int kSmallGreedyPasses = 10;  // ... of a graph whose greedy runs here
 constexpr int kSmallChunk = 32;    // most arcs of a chunk
 constexpr int kSmallTinyChunk = 16;            // ... of a graph of at most
 constexpr int64_t kSmallTinyArcs = 32 << 10;   // this many arcs
@@ -443,7 +444,11 @@ enum SmallKind { kScoreChain, kGainChain, kMissChain };
 template <int P, int J, bool WGT>
 static void small_launch(const void *args, SmallKind kind, int grid, size_t lds,
                          hipStream_t st) {
-  if (kind == kMissChain)
+  if constexpr (P > kSmallGreedyPasses) {
+    if (kind != kScoreChain) throw HipError{GED_ERR_ARG, "greedy chain of too many passes"};
+    hipLaunchKernelGGL((k_small_chain<P, J, WGT, false>), dim3(grid), dim3(kSmallThreads), lds, st,
+                       *static_cast<const SmallArgs *>(args));
+  } else if (kind == kMissChain)
     hipLaunchKernelGGL((k_small_miss<P, J, WGT>), dim3(grid), dim3(kSmallThreads), lds, st,
                        *static_cast<const SmallMissArgs *>(args));
   else if (kind == kGainChain)
@@ -504,11 +509,24 @@ static SmallGraph &small_graph(ged_graph *g) {
   return *g->small;
 }
 
-bool small_batch_ok(ged_graph *g) {
-  return g->n <= kSmallVertices && g->nnz <= kSmallBatchArcs && small_graph(g).ok;
+bool small_batch_ok(ged_graph *g, int groups) {
+  if (g->n > kSmallVertices || g->nnz > kSmallBatchArcs) return false;
+  if (groups <= kSmallFewGroups) {
+    if (g->weighted && g->n > kSmallFewWeighted && g->nnz > kSmallFewWeightedArcs) return false;
+    if (g->flags == GED_DIRECTED && g->n > kSmallFewDirected) return false;
+  }
+  return small_graph(g).ok;
 }
 
-bool small_score_ok(ged_graph *g) { return g->nnz <= kSmallScoreArcs && small_batch_ok(g); }
+bool small_score_ok(ged_graph *g) {
+  return g->n <= (g->weighted ? kSmallScoreWeighted : kSmallScoreVertices) &&
+         g->nnz <= kSmallScoreArcs && small_graph(g).ok;
+}
+
+bool small_greedy_ok(ged_graph *g) {
+  return g->n <= kSmallGreedyVertices && g->nnz <= kSmallScoreArcs && small_graph(g).ok &&
+         small_graph(g).passes <= kSmallGreedyPasses;
+}
 
 void small_scores(ged_graph *g, const int64_t *offs, const int *mem, int groups, double *out,
                   hipStream_t st, int n_inline) {
