@@ -637,6 +637,18 @@ static int create_impl(int64_t n, int64_t nnz, const int64_t *row_ptr, const int
         g->hc_rows_l = h;
     }
   }
+  if (flags == GED_UNDIRECTED && !weights && g->max_deg > kPushHubDegree) {
+    // stored by decreasing degree, unless the caller's order was kept
+    int lo = 0, hi = (int)n;
+    while (!keep_order && lo < hi) {
+      const int v = (lo + hi) / 2;
+      if (hc.irp[(size_t)v + 1] - hc.irp[(size_t)v] > kPushHubDegree)
+        lo = v + 1;
+      else
+        hi = v;
+    }
+    g->push_hubs = hi;
+  }
   const std::vector<int> &irp = hc.irp, &ici = hc.ici, &orp = hc.orp, &oci = hc.oci;
   const std::vector<double> &iw = hc.iw, &ow = hc.ow;
   return guarded([&]() -> int {

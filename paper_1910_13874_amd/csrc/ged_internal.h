@@ -159,6 +159,12 @@ constexpr int kRowsPerBlock = 255;     // max rows of one row block (row_ptr sli
 // 1/kHubShareDiv of the arcs (StepArgs::hc_rows).
 constexpr int kHubRows = 2048;
 constexpr int kHubShareDiv = 10;
+// Tile pushes test targets of more than this degree as members of their
+// column: a member takes one add per neighbour, all at one address.  BA
+// n = 300,000, 256 groups with 20 (3, none) of the 64 highest-degree vertices
+// each: 5.94 (2.38, 1.17) ms without the test, 4.94 (2.19, 1.17) at 512, 4.75
+// (2.17, 1.18) here; every target tested, as before: 4.75 (2.11, 1.43).
+constexpr int kPushHubDegree = 128;
 constexpr int kSegDoubles = 8192;      // nnz*C handled by one long-row segment
 
 // Row partition for a step with C columns: row blocks of consecutive short
@@ -638,6 +644,7 @@ struct ged_graph {
   int32_t count16 = 0;
   int c16_least_hub = -1;       // 1 + the last vertex with omega_2 > kC16Max (-1: not known)
   int c16_used = -1;            // hub cut of the last batch's tiles (-1: 32-bit counts)
+  int push_hubs = 0;            // vertices below it have more than kPushHubDegree arcs
   int hc_rows = 0;              // rows of the LDS copy in C = 1 count steps (kHubRows or 0)
   // registered with a server at (served_alpha, served_eps): other values,
   // invalidation and a change of tail bound are refused until it is destroyed

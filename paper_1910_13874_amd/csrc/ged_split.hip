@@ -258,10 +258,11 @@ __device__ __forceinline__ void clear_entry(const int *__restrict__ rp,
 // stores zeros instead.  NEXT: wl_next is used (the adds return the old
 // count); otherwise the adds return nothing and the wave does not wait.  The
 // level-2 push also fixes the member rows (fx): it neither reads nor writes
-// them, and the member pushes before it have finished.  CHECK false: the
-// adds go to member rows too (their sums stay within omega_2) and the caller
-// fixes them after the launch; a tile's push then makes one random access per
-// arc instead of two, beside a dense step that its accesses slow down.
+// them, and the member pushes before it have finished.  CHECK false: only
+// targets below `hubs` (graph's push_hubs) are tested; the adds go to other
+// member rows too (their sums stay within omega_2) and the caller fixes them
+// after the launch.  A tile's push then makes about one random access per arc
+// instead of two, beside a dense step that its accesses slow down.
 template <class CT, bool CLEAR, bool NEXT, bool CHECK = true>
 __global__ __launch_bounds__(kBlock) void k_push_wl(const int *__restrict__ rp,
                                                     const int *__restrict__ ci, int C,
@@ -270,7 +271,7 @@ __global__ __launch_bounds__(kBlock) void k_push_wl(const int *__restrict__ rp,
                                                     const uint64_t *__restrict__ tmask,
                                                     uint64_t *wl_next, unsigned *wl_next_n,
                                                     unsigned wl_next_cap, MemberFix<CT> fx,
-                                                    int h16) {
+                                                    int h16, int hubs) {
   fix_members(fx);
   const unsigned count = min(*wl_n, wl_cap);  // capacities are sized to never overflow
   // A chunk is at most U arcs per lane: every col_idx load of the chunk is
@@ -292,9 +293,12 @@ __global__ __launch_bounds__(kBlock) void k_push_wl(const int *__restrict__ rp,
     int x[U];
 #pragma unroll
     for (int k = 0; k < U; ++k) x[k] = j0 + 64 * k < j1 ? ci[j0 + 64 * k] : -1;
+    uint64_t tm[U];
+#pragma unroll
+    for (int k = 0; k < U; ++k) tm[k] = x[k] >= 0 && (CHECK || x[k] < hubs) ? tmask[x[k]] : 0;
     bool out[U];
 #pragma unroll
-    for (int k = 0; k < U; ++k) out[k] = x[k] >= 0 && (!CHECK || !((tmask[x[k]] >> c) & 1ull));
+    for (int k = 0; k < U; ++k) out[k] = x[k] >= 0 && !((tm[k] >> c) & 1ull);
     const CT v = src[(size_t)y * C + c];
     if (!NEXT) {
 #pragma unroll
@@ -988,17 +992,17 @@ static void push_phase(ged_graph *g, SplitWs &w, const SplitPlan &pl, int C, con
     if (wl3)
       hipLaunchKernelGGL((k_push_wl<CT, false, true>), dim3(w.wl_blocks), dim3(kBlock), 0, st, rp,
                          ci, C, c1, c2, w.wl.as<const uint64_t>(), w.wl_n.as<const unsigned>(),
-                         w.wl_cap, tmask, wl3, wl3_n, w.wl3_cap, fx, h16);
+                         w.wl_cap, tmask, wl3, wl3_n, w.wl3_cap, fx, h16, 0);
     else if (C == 1)
       hipLaunchKernelGGL((k_push_wl<CT, false, false>), dim3(w.wl_blocks), dim3(kBlock), 0, st,
                          rp, ci, C, c1, c2, w.wl.as<const uint64_t>(),
                          w.wl_n.as<const unsigned>(), w.wl_cap, tmask, (uint64_t *)nullptr,
-                         (unsigned *)nullptr, 0u, fx, h16);
+                         (unsigned *)nullptr, 0u, fx, h16, 0);
     else
       hipLaunchKernelGGL((k_push_wl<CT, false, false, false>), dim3(w.wl_blocks), dim3(kBlock), 0,
                          st, rp, ci, C, c1, c2, w.wl.as<const uint64_t>(),
                          w.wl_n.as<const unsigned>(), w.wl_cap, tmask, (uint64_t *)nullptr,
-                         (unsigned *)nullptr, 0u, MemberFix<CT>(), h16);
+                         (unsigned *)nullptr, 0u, MemberFix<CT>(), h16, g->push_hubs);
   }
   // member rows after an unchecked push, or where there was none
   if (!c2 || (!wl3 && C > 1)) {
@@ -1011,7 +1015,7 @@ static void push_phase(ged_graph *g, SplitWs &w, const SplitPlan &pl, int C, con
     hipLaunchKernelGGL((k_push_wl<CT, false, false>), dim3(kWl3Grid), dim3(kBlock), 0, st, rp, ci, C,
                        static_cast<const CT *>(c2), l3, w.wl3.as<const uint64_t>(),
                        w.wl3_n.as<const unsigned>(), w.wl3_cap, tmask, (uint64_t *)nullptr,
-                       (unsigned *)nullptr, 0u, MemberFix<CT>(), -1);
+                       (unsigned *)nullptr, 0u, MemberFix<CT>(), -1, 0);
     GED_HIP(hipGetLastError());
   }
 }
@@ -1034,7 +1038,7 @@ static void clear_phase(ged_graph *g, SplitWs &w, const SplitPlan &pl, int C,
     hipLaunchKernelGGL((k_push_wl<CT, true, false>), dim3(w.wl_blocks), dim3(kBlock), 0, st, rp, ci, C,
                        c1, c2, w.wl.as<const uint64_t>(), w.wl_n.as<const unsigned>(), w.wl_cap,
                        tmask, (uint64_t *)nullptr, (unsigned *)nullptr, 0u, MemberFix<CT>(),
-                       h16);
+                       h16, 0);
     GED_HIP(hipGetLastError());
   }
   hipLaunchKernelGGL(k_clear_members<CT>, dim3(mgrid), dim3(kBlock), 0, st, rp, ci, offs, mem,

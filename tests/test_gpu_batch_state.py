@@ -173,3 +173,31 @@ def test_more_groups_than_one_launch(ged):
     one = np.array([oracle.score(g, np.array([v], np.int32), alpha, eps)[0] for v in range(g.n)])
     assert (np.abs(s - one[mem]) <= REL * one[mem]).all()  # isolated vertices score 0
     gg.close()
+
+
+@pytest.mark.parametrize("keep_order", [False, True])
+@pytest.mark.parametrize("tile,count16", [(2, -1), (8, 0), (64, -1), (64, 0)])
+def test_pushed_tiles_with_member_hubs(ged, keep_order, tile, count16):
+    """Pushed tiles whose groups hold hubs (tested as members by the push),
+    their neighbours and vertices around the test's degree line (128), in the
+    32-bit and the 16-bit layout and with the caller's vertex order."""
+    g = inputs.barabasi_albert(40_000, 3, 12)
+    gg = ged.GedGraph.from_graph(g, keep_order=keep_order)
+    gg.set_batch_tile(tile)
+    gg.set_batch_row_cut(1)
+    if count16 < 0:
+        gg.set_count16(-1)
+    by_deg = np.argsort(-g.degrees, kind="stable").astype(np.int32)
+    line = int((g.degrees > 128).sum())
+    assert 8 < line < 2000
+    hub = by_deg[0]
+    groups = [by_deg[:1], by_deg[:20], by_deg[line - 2:line + 2], by_deg[line:line + 1],
+              np.concatenate([[hub], g.col_idx[g.row_ptr[hub]:g.row_ptr[hub + 1]][:50]]),
+              inputs.group(g.n, 30, 4)] + [np.concatenate([by_deg[j:j + 1], inputs.group(g.n, 20, j)])
+                                           for j in range(2, 70)]
+    groups = [np.unique(S).astype(np.int32) for S in groups]
+    alpha, eps = g.default_alpha(), 1e-4
+    s = gg.score_batch(*flat(groups), alpha, eps)
+    for j in list(range(8)) + [40, 73]:
+        assert rel(s[j], oracle.score(g, groups[j], alpha, eps)[0]) <= REL, (tile, j)
+    gg.close()
