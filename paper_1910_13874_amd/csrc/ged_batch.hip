@@ -71,9 +71,9 @@ void batch_forget(const ged_graph *g) {
 // The race both autotuners run: every candidate width at the threshold the
 // caller fixed (or the full LDS capacity), then -- when the threshold is left
 // to the tuner -- thresholds of 1/2 and 1/4 of the capacity at the chosen
-// width.  time_per_col(C, cut_div) returns milliseconds per column, or throws
-// HipError{GED_ERR_NOMEM} when the width does not fit (wider ones are then
-// skipped).  A candidate replaces the best so far only if it is faster per
+// width.  time_per_col(C, cut_div, best) returns milliseconds per column, or
+// throws HipError{GED_ERR_NOMEM} when the width does not fit (wider ones are
+// then skipped); `best` is the fastest so far.  A candidate replaces the best so far only if it is faster per
 // column by the factor `margin` (wider tiles hold more memory and leave more
 // columns idle in a batch's last tile; lower thresholds add segments).
 template <class F>
@@ -90,7 +90,7 @@ static int race_tile(ged_graph *g, std::initializer_list<int> widths, double mar
   for (int C : ws) {
     double t;
     try {
-      t = time_per_col(C, cut0);
+      t = time_per_col(C, cut0, best);
     } catch (const HipError &e) {
       if (e.code != GED_ERR_NOMEM) throw;
       break;  // wider tiles do not fit either
@@ -102,7 +102,7 @@ static int race_tile(ged_graph *g, std::initializer_list<int> widths, double mar
   }
   if (g->batch_cut_div == 0)
     for (int d : {2, 4}) {
-      const double t = time_per_col(best_c, d);
+      const double t = time_per_col(best_c, d, best);
       if (t < best * 0.97) {
         best = t;
         best_cut = d;
@@ -124,7 +124,7 @@ static int autotune_tile(ged_graph *g, BatchWs &b) {
   hipEvent_t e0, e1;
   GED_HIP(hipEventCreate(&e0));
   GED_HIP(hipEventCreate(&e1));
-  auto timed = [&](int C, int cut) -> double {
+  auto timed = [&](int C, int cut, double) -> double {
     Partition &p = partition(g, C, false, cut);
     StepWs ws;
     ws.fit(p, st);
@@ -165,7 +165,8 @@ static int autotune_tile(ged_graph *g, BatchWs &b) {
 
 // Split scoring: the same race over the dense levels of a split tile (the
 // level-(s+1) step on count rows and the combining step), at C = 8..64; best
-// of two timed passes after a warm-up.
+// of two timed passes after a warm-up, or the first where it is a quarter
+// behind.
 static int autotune_split(ged_graph *g, BatchWs &b, const SplitPlan &pl0, double push2_per_group,
                           int64_t max_group) {
   if (g->batch_tile > 0 && g->batch_cut_div > 0) return g->batch_tile;
@@ -173,7 +174,7 @@ static int autotune_split(ged_graph *g, BatchWs &b, const SplitPlan &pl0, double
   hipEvent_t e0, e1;
   GED_HIP(hipEventCreate(&e0));
   GED_HIP(hipEventCreate(&e1));
-  auto timed = [&](int C, int cut) -> double {
+  auto timed = [&](int C, int cut, double best) -> double {
     SplitPlan pl = pl0;
     pl.cut_div = cut;
     pl.c16_hub = split_c16_hub(g, pl, C, st);
@@ -190,6 +191,7 @@ static int autotune_split(ged_graph *g, BatchWs &b, const SplitPlan &pl0, double
       float t = 0.f;
       GED_HIP(hipEventElapsedTime(&t, e0, e1));
       ms = std::min(ms, t);
+      if (ms / C > 1.25 * best) break;
     }
     return ms / C;
   };
@@ -312,7 +314,7 @@ int score_batch(ged_graph *g, const int64_t *offsets, const int32_t *members, in
   pl.cut_div = g->batch_cut_div;
   if (split) pl.c16_hub = split_c16_hub(g, pl, C, st);
   g->c16_used = pl.c16_hub;
-  b.ws.fit(partition(g, C, false, g->batch_cut_div), st);
+  if (!split) b.ws.fit(partition(g, C, false, g->batch_cut_div), st);
   // internal ids, duplicates inside a group dropped; column of every member
   std::vector<int64_t> &hoff = b.h_offsets;
   std::vector<int> &hmem = b.h_members;

@@ -1553,14 +1553,19 @@ void plan_partition(PartitionPlan &pl, const int *rp, const int *ci, int n, int 
       ++r;
       continue;
     }
-    const int r0 = r;
-    int acc = 0;
-    while (r < n && r - r0 < kRowsPerBlock) {
-      const int d = rp[r + 1] - rp[r];
-      if (d > nnz_blk || acc + d > nnz_blk) break;
-      acc += d;
-      ++r;
+    // the block takes rows while its arcs fit: the last row pointer within
+    // rp[r0] + nnz_blk, found by doubling steps and then by halving (row by row
+    // this was 0.7 ms per partition of 10^6 rows in a first call)
+    const int r0 = r, rmax = std::min(n, r0 + kRowsPerBlock);
+    const int64_t last = (int64_t)rp[r0] + nnz_blk;
+    int hi = ++r, step = 1;  // row r0 fits; rp[r] <= last throughout
+    while (hi < rmax && rp[hi] <= last) {
+      r = hi;
+      hi = std::min(rmax, hi + step);
+      step *= 2;
     }
+    r = (int)(std::upper_bound(rp + r, rp + hi + 1, last,
+                               [](int64_t v, int x) { return v < x; }) - rp) - 1;
     pl.blocks.insert(pl.blocks.end(), {r0, r, rp[r0], rp[r]});
   }
   pl.n_blocks = (int)pl.blocks.size() / 4;

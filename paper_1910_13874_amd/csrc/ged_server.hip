@@ -24,6 +24,7 @@
 // holds afterwards stays counted.
 #include <algorithm>
 #include <chrono>
+#include <cmath>
 #include <condition_variable>
 #include <cstring>
 #include <deque>
@@ -160,8 +161,14 @@ static void lane_setup(Lane &L, int C) {
     // each) fit C * (nnz/512 + 1) + 2n entries; one larger group grows it
     const size_t cap = (size_t)C * split_wl_need(g, 0) + 2 * (size_t)n;
     split_fit(g, L.sw, L.pl, C, cap, L.st);
-    // a tile runs at the narrowest power-of-two width that holds its requests
-    for (int w = 1; w < C; w *= 2) split_fit_width(g, L.sw, L.pl, w, L.st);
+    // a tile runs at the narrowest power-of-two width that holds its requests,
+    // with level 2 pushed or gathered
+    SplitPlan gathered = L.pl;
+    gathered.dense2 = split_dense2(g, L.pl, C, INFINITY);
+    for (int w = 1; w <= C; w *= 2) {
+      split_fit_width(g, L.sw, L.pl, w, L.st);
+      if (gathered.dense2) split_fit_width(g, L.sw, gathered, w, L.st);
+    }
     L.tmask.ensure(sizeof(uint64_t) * (size_t)n);
     L.acc.ensure(sizeof(double) * 64);
     L.h_acc.ensure(sizeof(double) * 64);

@@ -720,6 +720,29 @@ static Partition &final_partition(ged_graph *g, const SplitPlan &pl, int C) {
                  : step_partition(g, pl, C, in);
 }
 
+// fn on every partition that split_dense and split_tile_reduce ask for at C
+// columns, and no other: each is planned on the host and uploaded, which a
+// first call and every candidate of a width race pay.
+template <class F>
+static void for_partitions(ged_graph *g, const SplitPlan &pl, int C, F &&fn) {
+  const bool g16 = pl.c16_hub >= 0 || pl.m16;
+  bool dense = false, narrow = false, quad = false;
+  if (pl.dense2) (pl.m16 ? quad : narrow) = true;
+  for (int i = pl.s + 1; i < pl.a; ++i) {
+    if (pl.lv32 && pl.push3 && i == pl.s + 1) continue;  // pushed
+    if (pl.s > 0 && i == pl.s + 1 && g16)
+      quad = true;
+    else if (pl.lv32 || (pl.s > 0 && i == pl.s + 1 && pl.c32))
+      narrow = true;
+    else
+      dense = true;
+  }
+  if (dense) fn(partition(g, C, false, pl.cut_div));
+  if (narrow) fn(step_partition(g, pl, C, IN_CNT32));
+  if (quad) fn(step_partition(g, pl, C, IN_CNT16));
+  fn(final_partition(g, pl, C));
+}
+
 // Eight lanes per row copy its lower arcs.
 __global__ __launch_bounds__(kBlock) void k_lower_copy(const int *__restrict__ rp,
                                                        const int *__restrict__ ci,
@@ -878,11 +901,8 @@ void split_fit(ged_graph *g, SplitWs &w, const SplitPlan &pl, int C, size_t wl_n
   const size_t nC = (size_t)g->n * C;
   const bool dirty = !w.state.zero();
   if (!counts_only) {
-    w.ws.fit(partition(g, C, false, pl.cut_div), st);
     // every partition split_dense asks for, built before any capture
-    w.ws.fit(step_partition(g, pl, C, IN_CNT32), st);
-    if (pl.c16_hub >= 0 || pl.m16) w.ws.fit(step_partition(g, pl, C, IN_CNT16), st);
-    w.ws.fit(final_partition(g, pl, C), st);
+    for_partitions(g, pl, C, [&](Partition &p) { w.ws.fit(p, st); });
   }
   if (pl.s >= 1) {
     const size_t cb = (pl.c32 ? sizeof(uint32_t) : sizeof(uint64_t)) * nC;
@@ -949,10 +969,7 @@ void split_fit(ged_graph *g, SplitWs &w, const SplitPlan &pl, int C, size_t wl_n
 // counts were fitted for a wider tile: the counts, levels and worklists of a
 // narrower tile use the first n * C entries of the same buffers.
 void split_fit_width(ged_graph *g, SplitWs &w, const SplitPlan &pl, int C, hipStream_t st) {
-  w.ws.fit(partition(g, C, false, pl.cut_div), st);
-  w.ws.fit(step_partition(g, pl, C, IN_CNT32), st);
-  if (pl.c16_hub >= 0) w.ws.fit(step_partition(g, pl, C, IN_CNT16), st);
-  w.ws.fit(final_partition(g, pl, C), st);
+  for_partitions(g, pl, C, [&](Partition &p) { w.ws.fit(p, st); });
 }
 
 template <class CT>
@@ -1055,8 +1072,8 @@ void split_dense(ged_graph *g, SplitWs &w, const SplitPlan &pl, int C, const uin
   const size_t nC = (size_t)n * C;
   const PrepCache &pc = g->prep;
   const double alpha = pc.alpha;
-  Partition &p = partition(g, C, false, pl.cut_div);
-  Partition &pn = step_partition(g, pl, C, IN_CNT32);  // 32-bit gathers (count levels)
+  // the partition of a step that gathers `in` (for_partitions lists them)
+  auto part = [&](int in) -> Partition & { return step_partition(g, pl, C, in); };
   const double *T = pc.t_levels.as<const double>();
   const SplitWs &cw = counts ? *counts : w;
   const void *c1 = pl.s >= 1 ? cw.cnt1.p : nullptr;
@@ -1090,17 +1107,16 @@ void split_dense(ged_graph *g, SplitWs &w, const SplitPlan &pl, int C, const uin
       a.Xc16 = cw.cnt1h.as<const uint16_t>();
       a.hub = 0;
       a.Y16 = cw.cnt2h.as<uint16_t>();
-      Partition &pq = step_partition(g, pl, C, IN_CNT16);
       if (profile)
-        run_step(g, pq, a, IN_CNT16, OUT_TILE32H, st);
+        run_step(g, part(IN_CNT16), a, IN_CNT16, OUT_TILE32H, st);
       else
-        launch_step(pq, a, IN_CNT16, OUT_TILE32H, st);
+        launch_step(part(IN_CNT16), a, IN_CNT16, OUT_TILE32H, st);
       a.Xc16 = cw.cnt2h.as<const uint16_t>();  // what level 3 gathers
       a.Y16 = nullptr;
     } else if (profile) {
-      run_step(g, pn, a, IN_CNT32, OUT_TILE32, st);
+      run_step(g, part(IN_CNT32), a, IN_CNT32, OUT_TILE32, st);
     } else {
-      launch_step(pn, a, IN_CNT32, OUT_TILE32, st);
+      launch_step(part(IN_CNT32), a, IN_CNT32, OUT_TILE32, st);
     }
     a.Y32 = nullptr;
   }
@@ -1133,7 +1149,6 @@ void split_dense(ged_graph *g, SplitWs &w, const SplitPlan &pl, int C, const uin
         a.hub = 0;
       }
       const int in = g16 ? IN_CNT16 : IN_CNT32;
-      Partition &pi = in == IN_CNT16 ? step_partition(g, pl, C, IN_CNT16) : pn;
       if (i < pl.a) {
         a.alpha = 1.0;
         a.inj = om + (size_t)(i - 3) * n;
@@ -1144,9 +1159,9 @@ void split_dense(ged_graph *g, SplitWs &w, const SplitPlan &pl, int C, const uin
         a.y32_marked = out == OUT_TILE32H && pl.nlv == 1 ? 1 : 0;
         if (pl.push3 && i == pl.s + 1) continue;  // pushed with the first levels
         if (profile)
-          run_step(g, pi, a, in, out, st);
+          run_step(g, part(in), a, in, out, st);
         else
-          launch_step(pi, a, in, out, st);
+          launch_step(part(in), a, in, out, st);
       } else {
         a.alpha = alpha_a;
         lower_args(i);
@@ -1204,13 +1219,12 @@ void split_dense(ged_graph *g, SplitWs &w, const SplitPlan &pl, int C, const uin
       a.alpha = alpha;
     }
     a.inj = T + (size_t)i * n;
-    Partition &ps = in == IN_CNT16 ? step_partition(g, pl, C, IN_CNT16) : in == IN_CNT32 ? pn : p;
     if (i < pl.a) {
       a.Y = lv + (size_t)(i - 1 - pl.s) * nC;
       if (profile)
-        run_step(g, ps, a, in, OUT_TILE, st);
+        run_step(g, part(in), a, in, OUT_TILE, st);
       else
-        launch_step(ps, a, in, OUT_TILE, st);
+        launch_step(part(in), a, in, OUT_TILE, st);
     } else {
       // absent inputs: index mask 0 into a valid buffer, weight 0
       const double *any = pc.tr.as<const double>();
@@ -1416,7 +1430,9 @@ int split_score(ged_graph *g, const int32_t *S, int32_t s_len, double *out) {
     for (int v : mem) b += g->push_bound[(size_t)v];
     pl.push3 = b <= (double)push3_max_arcs(g);
   }
-  if (pl.s == 2 && !pl.push3) {
+  // omega_2 is at most degree times largest degree: the table is read (and,
+  // the first time, copied to the host) only where that would gather
+  if (split_dense2(g, pl, 1, (double)deg_sum * g->max_deg)) {
     const std::vector<double> &om2 = omega2_host(g, st);
     double v = 0.0;
     for (int x : mem) v += om2[(size_t)x];
