@@ -213,18 +213,17 @@ struct Partition {
   int n_grid2 = 0;   // blocks after the row blocks: segments, or bucket blocks
   int n_long = 0;    // long rows
   int64_t bucket_rows = 0;  // 0: long rows cut into segments, else source buckets
-  DBuf blocks;       // int4 [n_blocks]: (row0, row1, nnz0, nnz1)
-  DBuf segs;         // int4 [n_grid2]: segments (row, nnz0, nnz1, long index), or
-                     // bucket blocks (piece0, piece1, arc0, arc1) in launch order
-  DBuf long_rows;    // int  [n_long]:   row id
-  DBuf long_first;   // int  [n_long+1]: first segment (or entry of bk_lsub) of each long row
+  const int4 *blocks = nullptr;  // [n_blocks]: (row0, row1, nnz0, nnz1)
+  const int4 *segs = nullptr;    // [n_grid2]: segments (row, nnz0, nnz1, long index), or
+                                 // bucket blocks (piece0, piece1, arc0, arc1) in launch order
+  const int *long_rows = nullptr;   // [n_long]:   row id
+  const int *long_first = nullptr;  // [n_long+1]: first segment (or entry of bk_lsub) of each
+                                    // long row
+  const int *bk_ptr = nullptr;   // [n_segs+1]: first arc of each piece in bk_ci
+  const int *bk_lsub = nullptr;  // [n_segs]: the pieces of each long row in (bucket, offset) order
+  DBuf mem;          // the arrays above, in one allocation and one copy
   DBuf bk_ci;        // int [arcs of long rows]: sources, piece by piece
-  DBuf bk_ptr;       // int [n_segs+1]: first arc of each piece in bk_ci
-  DBuf bk_lsub;      // int [n_segs]: the pieces of each long row in (bucket, offset) order
-  size_t device_bytes() const {
-    return blocks.bytes + segs.bytes + long_rows.bytes + long_first.bytes + bk_ci.bytes +
-           bk_ptr.bytes + bk_lsub.bytes;
-  }
+  size_t device_bytes() const { return mem.bytes + bk_ci.bytes; }
 };
 
 // Host plan of a partition (what build_partition uploads).

@@ -1295,26 +1295,26 @@ static void launch_t(const Partition &p, const StepArgs &a, hipStream_t st, hipE
   const bool bk = p.bucket_rows > 0 && p.n_grid2 > 0;
   if (bk && C > 8) throw HipError{GED_ERR_ARG, "source buckets at more than 8 columns"};
   b.bk_ci = bk ? p.bk_ci.as<const int>() : nullptr;
-  b.bk_ptr = bk ? p.bk_ptr.as<const int>() : nullptr;
-  b.long_rows = p.long_rows.as<const int>();
-  b.long_first = p.long_first.as<const int>();
+  b.bk_ptr = bk ? p.bk_ptr : nullptr;
+  b.long_rows = p.long_rows;
+  b.long_first = p.long_first;
   // single-column count steps keep the launch at any size: the extra code
   // alone slowed R-MAT scale 22's by 3 %
   if (p.n_segs > kInlineFixSegs || (C == 1 && IN == IN_CNT32 && !WGT)) b.seg_cnt = nullptr;
   if (grid > 0)
     hipLaunchKernelGGL((k_step<C, IN, OUT, WGT>), dim3(grid), dim3(kBlock), 0, st, b,
-                       p.blocks.as<const int4>(), p.segs.as<const int4>(), p.n_blocks);
+                       p.blocks, p.segs, p.n_blocks);
   if (ev) GED_HIP(hipEventRecord(ev, st));
   if (p.n_long > 0 && bk) {
     const int rows_per_block = kBlock / 64;
     hipLaunchKernelGGL((k_fixup_pieces<C, OUT>),
                        dim3((p.n_long + rows_per_block - 1) / rows_per_block), dim3(kBlock), 0, st,
-                       b, p.long_rows.as<const int>(), p.long_first.as<const int>(),
-                       p.bk_lsub.as<const int>(), p.n_long);
+                       b, p.long_rows, p.long_first,
+                       p.bk_lsub, p.n_long);
   } else if (p.n_long > 0 && !b.seg_cnt) {
     const int thr = p.n_long * C;
     hipLaunchKernelGGL((k_fixup<C, OUT>), dim3((thr + kBlock - 1) / kBlock), dim3(kBlock), 0, st,
-                       b, p.long_rows.as<const int>(), p.long_first.as<const int>(), p.n_long);
+                       b, p.long_rows, p.long_first, p.n_long);
   }
 }
 
@@ -1593,19 +1593,28 @@ void build_partition(Partition &p, const std::vector<int> &rp, int C, int units,
   p.n_grid2 = pl.n_grid2;
   p.n_long = pl.n_long;
   p.bucket_rows = pl.bucket_rows;
-  auto up = [](DBuf &d, const std::vector<int> &v) {
-    d.ensure(sizeof(int) * std::max<size_t>(4, v.size()));
-    if (!v.empty())
-      GED_HIP(hipMemcpy(d.p, v.data(), sizeof(int) * v.size(), hipMemcpyHostToDevice));
+  std::vector<int> all;  // each array from a multiple of four ints on
+  auto put = [&all](const std::vector<int> &v) {
+    const size_t at = all.size();
+    all.insert(all.end(), v.begin(), v.end());
+    all.resize((all.size() + 7) & ~size_t(3));  // never empty
+    return at;
   };
-  up(p.blocks, pl.blocks);
-  up(p.segs, pl.grid2);
-  up(p.long_rows, pl.long_rows);
-  up(p.long_first, pl.long_first);
-  if (p.bucket_rows > 0) {
-    up(p.bk_ci, pl.bk_ci);
-    up(p.bk_ptr, pl.bk_ptr);
-    up(p.bk_lsub, pl.bk_lsub);
+  const size_t at[6] = {put(pl.blocks),     put(pl.grid2),  put(pl.long_rows),
+                        put(pl.long_first), put(pl.bk_ptr), put(pl.bk_lsub)};
+  p.mem.ensure(sizeof(int) * all.size());
+  GED_HIP(hipMemcpy(p.mem.p, all.data(), sizeof(int) * all.size(), hipMemcpyHostToDevice));
+  const int *d = p.mem.as<const int>();
+  p.blocks = reinterpret_cast<const int4 *>(d + at[0]);
+  p.segs = reinterpret_cast<const int4 *>(d + at[1]);
+  p.long_rows = d + at[2];
+  p.long_first = d + at[3];
+  p.bk_ptr = d + at[4];
+  p.bk_lsub = d + at[5];
+  if (p.bucket_rows > 0 && !pl.bk_ci.empty()) {
+    p.bk_ci.ensure(sizeof(int) * pl.bk_ci.size());
+    GED_HIP(hipMemcpy(p.bk_ci.p, pl.bk_ci.data(), sizeof(int) * pl.bk_ci.size(),
+                      hipMemcpyHostToDevice));
   }
 }
 
