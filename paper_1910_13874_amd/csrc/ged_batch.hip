@@ -174,13 +174,17 @@ static int autotune_split(ged_graph *g, BatchWs &b, const SplitPlan &pl0, double
   hipEvent_t e0, e1;
   GED_HIP(hipEventCreate(&e0));
   GED_HIP(hipEventCreate(&e1));
-  auto timed = [&](int C, int cut, double best) -> double {
+  auto fit = [&](int C, int cut) {
     SplitPlan pl = pl0;
     pl.cut_div = cut;
     pl.c16_hub = split_c16_hub(g, pl, C, st);
     pl.dense2 = split_dense2(g, pl, C, push2_per_group * C);
     pl.m16 = split_m16(g, pl, C, max_group);
     split_fit(g, b.sw, pl, C, 1, st);
+    return pl;
+  };
+  auto timed = [&](int C, int cut, double best) -> double {
+    const SplitPlan pl = fit(C, cut);
     split_dense(g, b.sw, pl, C, b.tmask.as<const uint64_t>(), st);  // warm-up
     float ms = 1e30f;
     for (int r = 0; r < 2; ++r) {
@@ -196,6 +200,15 @@ static int autotune_split(ged_graph *g, BatchWs &b, const SplitPlan &pl0, double
     return ms / C;
   };
   try {
+    if (g->batch_tile == 0) {
+      // the widest candidate's buffers first, so that no width grows them
+      // again (each growth frees and allocates all of them)
+      try {
+        fit(64, g->batch_cut_div > 0 ? g->batch_cut_div : 1);
+      } catch (const HipError &e) {
+        if (e.code != GED_ERR_NOMEM) throw;
+      }
+    }
     const int C = race_tile(g, {8, 16, 32, 64}, 0.97, timed);
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
