@@ -413,11 +413,10 @@ __device__ __forceinline__ void block_max_sum(unsigned long long &m, unsigned lo
   }
 }
 
-// *sum (zeroed by the caller) receives sum_v omega_2(v); out_d the values as
-// doubles (exact: omega_2 <= max_deg^2 < 2^53 wherever they are read).
+// *sum (zeroed by the caller) receives sum_v omega_2(v).
 __global__ __launch_bounds__(kBlock) void k_omega2(const int *__restrict__ rp,
                                                    const int *__restrict__ ci, int n,
-                                                   unsigned long long *out, double *out_d,
+                                                   unsigned long long *out,
                                                    unsigned long long *sum) {
   const int lane = threadIdx.x & 63;
   const int64_t nw = (int64_t)gridDim.x * (kBlock / 64);
@@ -429,10 +428,7 @@ __global__ __launch_bounds__(kBlock) void k_omega2(const int *__restrict__ rp,
       s += (unsigned long long)(rp[u + 1] - rp[u]);
     }
     for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-    if (lane == 0) {
-      out[v] = s;
-      out_d[v] = (double)s;
-    }
+    if (lane == 0) out[v] = s;
     acc += s;
   }
   block_max_sum(m, acc);
@@ -535,7 +531,6 @@ static void ensure_omega2(ged_graph *g, hipStream_t st) {
   if (g->omega2_ready) return;
   const int64_t n = g->n;
   g->omega2.ensure(sizeof(uint64_t) * (size_t)n);
-  g->omega2_f.ensure(sizeof(double) * (size_t)n);
   DBuf sum;
   sum.ensure(sizeof(unsigned long long));
   launch_fill_i32(sum.as<int>(), 0, 2, st);
@@ -543,7 +538,7 @@ static void ensure_omega2(ged_graph *g, hipStream_t st) {
       1, std::min<int64_t>(2048, (n + kBlock / 64 - 1) / (kBlock / 64)));
   hipLaunchKernelGGL(k_omega2, dim3(og), dim3(kBlock), 0, st, g->rp.as<const int>(),
                      g->ci.as<const int>(), (int)n, g->omega2.as<unsigned long long>(),
-                     g->omega2_f.as<double>(), sum.as<unsigned long long>());
+                     sum.as<unsigned long long>());
   GED_HIP(hipGetLastError());
   unsigned long long hs = 0;
   GED_HIP(hipMemcpyAsync(&hs, sum.p, sizeof(hs), hipMemcpyDeviceToHost, st));
@@ -552,6 +547,29 @@ static void ensure_omega2(ged_graph *g, hipStream_t st) {
   g->omega_sum[1] = (double)g->nnz;
   g->omega_sum[2] = (double)hs;
   g->omega2_ready = true;
+}
+
+__global__ void k_u64_to_f64(const unsigned long long *__restrict__ in, int64_t n, double *out) {
+  for (int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; v < n;
+       v += (int64_t)gridDim.x * blockDim.x)
+    out[v] = (double)in[v];
+}
+
+// omega_2 as doubles, for graphs that gather a level 2 (exact: counts that
+// fit 32 bits there).  Complete on return the first time, for any stream.
+static void ensure_omega2_f(ged_graph *g, hipStream_t st) {
+  std::lock_guard<std::mutex> lk(g_omega_mu);
+  if (g->omega2_f.p) return;
+  ensure_omega2(g, st);
+  DBuf f;
+  f.ensure(sizeof(double) * (size_t)g->n);
+  hipLaunchKernelGGL(k_u64_to_f64, dim3(grid_for((g->n + kBlock - 1) / kBlock, 8192)),
+                     dim3(kBlock), 0, st, g->omega2.as<const unsigned long long>(), g->n,
+                     f.as<double>());
+  GED_HIP(hipGetLastError());
+  GED_HIP(hipStreamSynchronize(st));
+  std::swap(g->omega2_f.p, f.p);
+  std::swap(g->omega2_f.bytes, f.bytes);
 }
 
 // The integer chain omega_3 .. omega_top from omega_2, written as doubles to
@@ -900,6 +918,7 @@ void split_fit(ged_graph *g, SplitWs &w, const SplitPlan &pl, int C, size_t wl_n
                hipStream_t st, bool counts_only) {
   const size_t nC = (size_t)g->n * C;
   const bool dirty = !w.state.zero();
+  if (pl.dense2) ensure_omega2_f(g, st);
   if (!counts_only) {
     // every partition split_dense asks for, built before any capture
     for_partitions(g, pl, C, [&](Partition &p) { w.ws.fit(p, st); });
@@ -969,6 +988,7 @@ void split_fit(ged_graph *g, SplitWs &w, const SplitPlan &pl, int C, size_t wl_n
 // counts were fitted for a wider tile: the counts, levels and worklists of a
 // narrower tile use the first n * C entries of the same buffers.
 void split_fit_width(ged_graph *g, SplitWs &w, const SplitPlan &pl, int C, hipStream_t st) {
+  if (pl.dense2) ensure_omega2_f(g, st);
   for_partitions(g, pl, C, [&](Partition &p) { w.ws.fit(p, st); });
 }
 
