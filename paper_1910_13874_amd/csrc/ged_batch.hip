@@ -472,7 +472,7 @@ int score_batch(ged_graph *g, const int64_t *offsets, const int32_t *members, in
                                    (const void *)(intptr_t)C,
                                    (const void *)(intptr_t)g->batch_cut_div,
                                    (const void *)(intptr_t)pl.c16_hub,
-                                   (const void *)(intptr_t)pl.dense2, g->omega2_f.p, g->ci_l.p,
+                                   (const void *)(intptr_t)pl.dense2, g->omega2_f.p, g->ci_l,
                                    (const void *)(intptr_t)pl.m16, b.sw.cnt1h.p, b.sw.cnt2h.p,
                                    b.sw2.cnt1h.p, b.sw2.cnt2h.p, b.sw.lv16.p};
   b.ws.key(sig);

@@ -603,7 +603,7 @@ struct ged_graph {
   std::mutex lower_mu;
   bool lower_ready = false;
   std::vector<int> h_rp_l;
-  ged::DBuf rp_l, ci_l;
+  int *rp_l = nullptr, *ci_l = nullptr;  // in ci's allocation, behind the arcs
   int hc_rows_l = 0;            // as hc_rows, for the lower arcs
   std::map<int, std::unique_ptr<ged::Partition>> parts_l;
   ged::PrepCache prep;

@@ -69,7 +69,7 @@ SplitPlan split_plan(const ged_graph *g, int ell) {
   // ell = 7 (one stored level) 61 -> 33 us per single-group step, but on ER
   // n = 10^4 (8 arcs per row, nine stored levels, 64 columns) the blocks only
   // get more rows, each a chain of loads: 24 -> 50 us.
-  p.quad = !g->weighted && p.r >= 1 && p.r < p.a && g->nnz >= 4 * g->n * std::max(1, p.nlv);
+  p.quad = g->rp_l && p.r >= 1 && p.r < p.a && g->nnz >= 4 * g->n * std::max(1, p.nlv);
   // count_2(x) <= omega_2(x) = sum_{y in N(x)} deg(y), which is at most
   // (max degree)^2, and at most nnz < 2^31 when no arc is listed twice
   p.c32 = g->max_deg < 65536 || g->simple;
@@ -778,13 +778,11 @@ void ensure_lower(ged_graph *g, hipStream_t st) {
   std::lock_guard<std::mutex> lk(g->lower_mu);
   if (g->lower_ready) return;
   const int n = (int)g->n;
-  g->rp_l.ensure(sizeof(int) * (size_t)(n + 1));
-  g->ci_l.ensure(sizeof(int) * (size_t)std::max<int64_t>(1, g->h_rp_l[(size_t)n]));
-  GED_HIP(hipMemcpyAsync(g->rp_l.p, g->h_rp_l.data(), sizeof(int) * (size_t)(n + 1),
+  GED_HIP(hipMemcpyAsync(g->rp_l, g->h_rp_l.data(), sizeof(int) * (size_t)(n + 1),
                          hipMemcpyHostToDevice, st));
   hipLaunchKernelGGL(k_lower_copy, dim3(grid_for(((int64_t)n + kBlock / 8 - 1) / (kBlock / 8), 65536)),
                      dim3(kBlock), 0, st, g->rp.as<const int>(), g->ci.as<const int>(),
-                     g->rp_l.as<const int>(), n, g->ci_l.as<int>());
+                     g->rp_l, n, g->ci_l);
   GED_HIP(hipGetLastError());
   GED_HIP(hipStreamSynchronize(st));
   g->lower_ready = true;
@@ -1112,8 +1110,8 @@ void split_dense(ged_graph *g, SplitWs &w, const SplitPlan &pl, int C, const uin
     a.inj = T + (size_t)(pl.quad ? i - 1 : i) * n;
     a.q_quad = pl.quad ? 1 : 0;
     if (!pl.quad) return;
-    a.rp = g->rp_l.as<const int>();
-    a.ci = g->ci_l.as<const int>();
+    a.rp = g->rp_l;
+    a.ci = g->ci_l;
     a.hc_rows = g->hc_rows_l;
   };
   if (pl.dense2) {
@@ -1518,7 +1516,7 @@ int split_score(ged_graph *g, const int32_t *S, int32_t s_len, double *out) {
           g->omega_lv.p, g->out_host.p, (const void *)st, abits, (const void *)(intptr_t)g->prep.ell,
           (const void *)(intptr_t)cap, (const void *)(uintptr_t)w.wl_cap,
           (const void *)(intptr_t)1 /* split */, (const void *)(intptr_t)pl.lv32,
-          (const void *)(intptr_t)pl.dense2, g->omega2_f.p, g->ci_l.p};
+          (const void *)(intptr_t)pl.dense2, g->omega2_f.p, g->ci_l};
       w.ws.key(sig);
       SplitExec &x = g->split_exec[(pl.push3 ? 1 : 0) + (staged ? 2 : 0) + (pl.lv32 ? 4 : 0) +
                                    (pl.dense2 ? 8 : 0)];
