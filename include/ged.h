@@ -66,7 +66,10 @@ typedef struct ged_graph ged_graph;
 
 /*
  * Create a graph handle from a host CSR (row_ptr int64[n+1], col_idx
- * int32[nnz]); the arrays are copied to device memory owned by the handle.
+ * int32[nnz]); the arrays are copied to device memory owned by the handle
+ * (undirected unweighted graphs of at least four arcs per vertex keep room for
+ * 4 (n + 1) + 2 nnz bytes more there: the arcs from lower to higher internal
+ * ids, which scores at odd walk lengths read).
  * flags: exactly one of GED_UNDIRECTED / GED_DIRECTED, optionally OR-ed with
  * GED_KEEP_ORDER.  Validation
  * (GED_ERR_GRAPH): row_ptr[0] == 0, non-decreasing, row_ptr[n] == nnz,

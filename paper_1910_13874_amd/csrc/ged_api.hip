@@ -201,13 +201,9 @@ double comb_bound(ged_graph *g, double alpha, double W_ell) {
 size_t score_bytes_held(const ged_graph *g) {
   size_t b = 0;
   for (const DBuf *d : {&g->mask, &g->vec[0], &g->vec[1], &g->s_levels, &g->acc, &g->s_dev,
-                        &g->sws.blk, &g->sws.seg, &g->sws.lng, &g->sws.red2,
-                        &g->split_ws.cnt1, &g->split_ws.cnt2, &g->split_ws.lv, &g->split_ws.wl,
-                        &g->split_ws.wl_n, &g->split_ws.wl3, &g->split_ws.wl3_n,
-                        &g->split_ws.ws.blk, &g->split_ws.ws.seg, &g->split_ws.ws.lng,
-                        &g->split_ws.ws.red2, &g->split_tmask, &g->split_in})
+                        &g->split_tmask, &g->split_in, &g->omega2_f})
     b += d->bytes;
-  return b;
+  return b + g->sws.bytes() + g->split_ws.bytes() + small_bytes(g);
 }
 
 int check_alpha_eps(ged_graph *g, double alpha, double eps) {

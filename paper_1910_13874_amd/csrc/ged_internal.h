@@ -535,6 +535,12 @@ struct SplitWs {
   int wl_blocks = 64;    // grid of the worklist kernels (any value is correct)
   TileState state;       // what cnt1, cnt2, wl_n and cnt1h hold between calls
   StepWs ws;
+  size_t bytes() const {
+    size_t b = ws.bytes();
+    for (const DBuf *d : {&cnt1, &cnt2, &lv, &cnt1h, &cnt2h, &lv16, &wl, &wl_n, &wl3, &wl3_n})
+      b += d->bytes;
+    return b;
+  }
 };
 
 
@@ -858,6 +864,7 @@ constexpr int64_t kSmallGreedyVertices = 10240;
 bool small_batch_ok(ged_graph *g, int groups);
 bool small_score_ok(ged_graph *g);
 bool small_greedy_ok(ged_graph *g);
+size_t small_bytes(const ged_graph *g);  // device bytes of its slices
 // Scores of groups (members mem[offs[g] .. offs[g+1]), internal ids; device
 // or coherent host memory) to out[groups], for the prepared (alpha, eps).
 // n_inline >= 0: one group, whose n_inline <= kSmallInline members mem (host)

@@ -175,8 +175,7 @@ static void lane_setup(Lane &L, int C) {
     launch_fill_i32(L.tmask.as<int>(), 0, (size_t)n * 2, L.st);
     GED_HIP(hipStreamSynchronize(L.st));
     L.sw.state.end(false);
-    L.bytes = L.tmask.bytes + L.sw.cnt1.bytes + L.sw.cnt2.bytes + L.sw.lv.bytes +
-              L.sw.wl.bytes + L.sw.ws.blk.bytes + L.sw.ws.seg.bytes + L.sw.ws.lng.bytes;
+    L.bytes = L.tmask.bytes + L.acc.bytes + L.sw.bytes() + L.ws.bytes();
     return;
   }
   L.X.ensure(sizeof(double) * (size_t)n * C);
@@ -194,8 +193,7 @@ static void lane_setup(Lane &L, int C) {
   L.fresh.assign(C, 0);
   L.launched.assign(C, 0);
   L.slot.assign(C, Req());
-  L.bytes = L.X.bytes + L.Y.bytes + L.tmask.bytes + L.ws.blk.bytes + L.ws.seg.bytes +
-            L.ws.lng.bytes;
+  L.bytes = L.X.bytes + L.Y.bytes + L.tmask.bytes + L.acc.bytes + L.state.bytes + L.ws.bytes();
 }
 
 // Complete request q (held_after: for a greedy request that ran, the bytes

@@ -528,6 +528,14 @@ bool small_greedy_ok(ged_graph *g) {
          small_graph(g).passes <= kSmallGreedyPasses;
 }
 
+size_t small_bytes(const ged_graph *g) {
+  if (!g->small) return 0;
+  size_t b = g->small->new_id.bytes;
+  for (const auto &side : g->small->buf)
+    for (const DBuf &d : side) b += d.bytes;
+  return b;
+}
+
 void small_scores(ged_graph *g, const int64_t *offs, const int *mem, int groups, double *out,
                   hipStream_t st, int n_inline) {
   const SmallGraph &sg = small_graph(g);
