@@ -294,7 +294,7 @@ int score_batch(ged_graph *g, const int64_t *offsets, const int32_t *members, in
   hipStream_t st = g->stream;
   // one workgroup per group where the graph is small, unless the caller fixed
   // the tiles or profiles their steps
-  if (!g->prof.on && !g->tile_fixed && !g->cut_fixed && g->count16 == 0 && small_batch_ok(g, G))
+  if (!g->prof.on && !g->tile_fixed && !g->cut_fixed && g->count16 == 0 && small_batch_ok(g))
     return small_batch(g, offsets, members, G, out);
   if (g->tile_nominal) {
     if (!g->tile_fixed) g->batch_tile = 0;

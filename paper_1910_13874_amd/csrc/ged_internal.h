@@ -839,11 +839,11 @@ int split_score(ged_graph *g, const int32_t *S, int32_t s_len, double *out);
 // are 16-bit ids and one vertex vector takes at most the CU's LDS.  A batch
 // pays up to 128 K arcs (n = 10^4, 80 K arcs, 256 groups: 700 us in tiles, 150
 // us so; below that the tile path costs a launch chain whatever its size).
-// A batch of at most 64 groups is one tile: the chain wins by the tile's
-// launches, and loses where a level of one group costs more than they do --
-// weighted arcs (10 bytes each) on the widest graphs (n = 18,000, 127 K arcs,
-// 64 groups: 258 us, in a tile 216; 79 K arcs: 193 and 293) and the widest
-// directed ones (n = 18,000, 40 K arcs, 64 groups: 198 and 181).
+// The choice is the graph's alone: a group's score has the same bits in every
+// batch.  A single tile of up to 64 groups is faster in one corner, the widest
+// graphs with many weighted arcs (n = 18,000, 127 K arcs: 64 groups 258 us,
+// in a tile 216; 256 groups 323 and 784) or directed ones (40 K arcs: 198 and
+// 181; 256 groups 389 and 879 at 65 K).
 //
 // A single group, one workgroup on one CU, pays up to 40 K arcs (a level of
 // 80 K takes it 6 us, a step 4 to 5) and while its level is not held up by the
@@ -855,13 +855,10 @@ int split_score(ged_graph *g, const int32_t *S, int32_t s_len, double *out);
 // 1,278 and 1,400 against 1,234 and 1,268, n = 18,000 1,763 against 1,248.
 constexpr int64_t kSmallVertices = 18000;
 constexpr int64_t kSmallBatchArcs = 128 << 10;
-constexpr int kSmallFewGroups = 64;
-constexpr int64_t kSmallFewWeighted = 14336, kSmallFewWeightedArcs = 96 << 10;
-constexpr int64_t kSmallFewDirected = 16384;
 constexpr int64_t kSmallScoreArcs = 40 << 10;
 constexpr int64_t kSmallScoreVertices = 8192, kSmallScoreWeighted = 6144;
 constexpr int64_t kSmallGreedyVertices = 10240;
-bool small_batch_ok(ged_graph *g, int groups);
+bool small_batch_ok(ged_graph *g);
 bool small_score_ok(ged_graph *g);
 bool small_greedy_ok(ged_graph *g);
 size_t small_bytes(const ged_graph *g);  // device bytes of its slices

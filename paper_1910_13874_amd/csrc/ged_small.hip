@@ -21,7 +21,8 @@
 // ER n = 10^4, 80 K arcs, 256 groups of 12 levels 119 us, about 13 cycles per
 // 64 reads) or, for a single group, by the chain of a level's latencies (ER
 // n = 1000: 21 us for 12 levels, whose members' values are requested ahead;
-// the step kernels took 65 us, 83 us per call against 36 us now).
+// the step kernels took 65 us, 83 us per call against 36 us now).  The first
+// such call of a process also loads this file's kernels (0.7 ms).
 #include <algorithm>
 #include <cstring>
 #include <numeric>
@@ -32,7 +33,11 @@ namespace ged {
 
 constexpr int kSmallThreads = 1024;
 constexpr int kSmallWaves = kSmallThreads / 64;
-constexpr int kSmallPasses = 18;   // most slices per wavefront (two registers each)
+// Most slices per wavefront.  A pass holds its row, slot, accumulator and
+// gathered sum, six registers; 16 wavefronts on a CU leave 128 per lane, so
+// from ten passes on the compiler spills some to scratch (the score kernels 20
+// of them at 10, 67 at 14, 147 at 18; with weights 30, 77, 177).
+constexpr int kSmallPasses = 18;
 constexpr int kSmallGreedyPasses = 10;  // ... of a graph whose greedy runs here
 constexpr int kSmallChunk = 32;    // most arcs of a chunk
 constexpr int kSmallTinyChunk = 16;            // ... of a graph of at most
@@ -126,7 +131,10 @@ __device__ __forceinline__ SmallLds small_lds(const SmallSide &s) {
 
 // The sources of a lane's chunks held in registers for the whole chain (J > 0:
 // chunks of at most 4J arcs), so that a level of a tiny graph waits for LDS
-// alone.
+// alone.  At four passes 45 of a score kernel's registers spill, and it is
+// still the better variant: directed n = 3,000, 24 K arcs 81 us against 88
+// with streamed sources and a greedy 1.56 ms against 1.88, ER n = 3,000 54 us
+// either way (greedy 0.94 and 1.06 ms); BA n = 3,000 36 us against 33.
 template <int P, int J>
 struct SmallCols {
   ushort4 c[P][J > 0 ? J : 1];
@@ -509,13 +517,8 @@ static SmallGraph &small_graph(ged_graph *g) {
   return *g->small;
 }
 
-bool small_batch_ok(ged_graph *g, int groups) {
-  if (g->n > kSmallVertices || g->nnz > kSmallBatchArcs) return false;
-  if (groups <= kSmallFewGroups) {
-    if (g->weighted && g->n > kSmallFewWeighted && g->nnz > kSmallFewWeightedArcs) return false;
-    if (g->flags == GED_DIRECTED && g->n > kSmallFewDirected) return false;
-  }
-  return small_graph(g).ok;
+bool small_batch_ok(ged_graph *g) {
+  return g->n <= kSmallVertices && g->nnz <= kSmallBatchArcs && small_graph(g).ok;
 }
 
 bool small_score_ok(ged_graph *g) {
