@@ -657,11 +657,19 @@ static int create_impl(int64_t n, int64_t nnz, const int64_t *row_ptr, const int
     // first score 0.3 ms
     const bool lower = !g->h_rp_l.empty() && nnz >= 4 * n;
     const size_t at = ((size_t)nnz + 63) & ~size_t(63);
-    const size_t room = lower ? at + (size_t)n + 1 + (size_t)g->h_rp_l[(size_t)n] : 0;
-    g->ci.ensure(sizeof(int) * std::max<size_t>({1, (size_t)nnz, room}));
     if (lower) {
+      const size_t room = at + (size_t)n + 1 + (size_t)g->h_rp_l[(size_t)n];
+      try {
+        g->ci.ensure(sizeof(int) * room);
+      } catch (const HipError &e) {
+        if (e.code != GED_ERR_NOMEM) throw;
+      }
+    }
+    if (g->ci.p) {
       g->rp_l = g->ci.as<int>() + at;
       g->ci_l = g->rp_l + n + 1;
+    } else {  // no room: odd lengths close over every arc
+      g->ci.ensure(sizeof(int) * (size_t)std::max<int64_t>(1, nnz));
     }
     GED_HIP(hipMemcpy(g->rp.p, irp.data(), sizeof(int) * (size_t)(n + 1), hipMemcpyHostToDevice));
     if (nnz > 0)

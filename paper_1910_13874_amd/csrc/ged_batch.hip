@@ -71,11 +71,12 @@ void batch_forget(const ged_graph *g) {
 // The race both autotuners run: every candidate width at the threshold the
 // caller fixed (or the full LDS capacity), then -- when the threshold is left
 // to the tuner -- thresholds of 1/2 and 1/4 of the capacity at the chosen
-// width.  time_per_col(C, cut_div, best) returns milliseconds per column, or
-// throws HipError{GED_ERR_NOMEM} when the width does not fit (wider ones are
-// then skipped); `best` is the fastest so far.  A candidate replaces the best so far only if it is faster per
-// column by the factor `margin` (wider tiles hold more memory and leave more
-// columns idle in a batch's last tile; lower thresholds add segments).
+// width.  time_per_col(C, cut_div, best) returns milliseconds per column
+// (`best`: the fastest so far), or throws HipError{GED_ERR_NOMEM} when the
+// width does not fit (wider ones are then skipped).  A candidate replaces the
+// best so far only if it is faster per column by the factor `margin` (wider
+// tiles hold more memory and leave more columns idle in a batch's last tile;
+// lower thresholds add segments).
 template <class F>
 static int race_tile(ged_graph *g, std::initializer_list<int> widths, double margin,
                      F &&time_per_col) {
@@ -202,11 +203,13 @@ static int autotune_split(ged_graph *g, BatchWs &b, const SplitPlan &pl0, double
   try {
     if (g->batch_tile == 0) {
       // the widest candidate's buffers first, so that no width grows them
-      // again (each growth frees and allocates all of them)
+      // again (each growth frees and allocates all of them); where they do not
+      // all fit, none of them stays in the narrower ones' way
       try {
         fit(64, g->batch_cut_div > 0 ? g->batch_cut_div : 1);
       } catch (const HipError &e) {
         if (e.code != GED_ERR_NOMEM) throw;
+        b.sw.release();
       }
     }
     const int C = race_tile(g, {8, 16, 32, 64}, 0.97, timed);

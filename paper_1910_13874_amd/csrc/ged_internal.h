@@ -541,6 +541,14 @@ struct SplitWs {
       b += d->bytes;
     return b;
   }
+  void release() {  // every buffer; as constructed
+    for (DBuf *d : {&cnt1, &cnt2, &lv, &cnt1h, &cnt2h, &lv16, &wl, &wl_n, &wl3, &wl3_n, &ws.blk,
+                    &ws.seg, &ws.lng, &ws.red2, &ws.cnt})
+      d->release();
+    wl_cap = wl3_cap = 0;
+    lv_zero = false;
+    state = TileState();
+  }
 };
 
 

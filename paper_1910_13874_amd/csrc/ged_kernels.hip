@@ -1309,8 +1309,7 @@ static void launch_t(const Partition &p, const StepArgs &a, hipStream_t st, hipE
     const int rows_per_block = kBlock / 64;
     hipLaunchKernelGGL((k_fixup_pieces<C, OUT>),
                        dim3((p.n_long + rows_per_block - 1) / rows_per_block), dim3(kBlock), 0, st,
-                       b, p.long_rows, p.long_first,
-                       p.bk_lsub, p.n_long);
+                       b, p.long_rows, p.long_first, p.bk_lsub, p.n_long);
   } else if (p.n_long > 0 && !b.seg_cnt) {
     const int thr = p.n_long * C;
     hipLaunchKernelGGL((k_fixup<C, OUT>), dim3((thr + kBlock - 1) / kBlock), dim3(kBlock), 0, st,

@@ -180,3 +180,34 @@ def test_small_graph_slices(name):
         y[v] = sum(part[first[m] + k:first[m + 1]:8].sum() for k in range(8))
     rows = np.repeat(np.arange(n), np.diff(rp))
     assert (y == np.bincount(rows, weights=x[ci], minlength=n).astype(np.int64)).all()
+
+
+def test_unchecked_tile_pushes():
+    """Tile pushes add to member rows below the hubs' test without asking: every
+    sum stays within omega_2 (so a 16-bit half of at most 2^16 - 2 never
+    carries), and rows outside the group hold the counts of the checked push.
+    Groups around hubs, their neighbours and each other."""
+    g = inputs.barabasi_albert(3000, 6, 8)
+    rp, ci = internal_csr(g)
+    n = g.n
+    deg = np.diff(rp)
+    hubs = int((deg > 128).sum())
+    assert 0 < hubs < n and (deg[:hubs] > 128).all()
+    rows = np.repeat(np.arange(n), deg)
+    omega2 = np.bincount(rows, weights=deg[ci], minlength=n).astype(np.int64)
+    rng = np.random.default_rng(2)
+    near = ci[rp[hubs]:rp[hubs + 1]]
+    for S in (np.array([0]), np.unique(near), np.unique(rng.integers(0, n, 400)),
+              np.arange(hubs + 40), np.arange(n)):
+        member = np.zeros(n, bool)
+        member[S] = True
+        cnt1 = np.bincount(ci[member[rows]], minlength=n)          # one per arc s -> y
+        cnt2 = np.bincount(ci[member[rows]], weights=deg[rows[member[rows]]], minlength=n)
+        src = ~member[rows] & (cnt1[rows] > 0)                      # arcs y -> x of the worklist
+        add = src & ~((ci < hubs) & member[ci])
+        cnt2 = (cnt2 + np.bincount(ci[add], weights=cnt1[rows[add]], minlength=n)).astype(np.int64)
+        assert (cnt2 <= omega2).all()
+        checked = src & ~member[ci]
+        want = np.bincount(ci[member[rows]], weights=deg[rows[member[rows]]], minlength=n) + \
+            np.bincount(ci[checked], weights=cnt1[rows[checked]], minlength=n)
+        assert (cnt2[~member] == want[~member]).all()
